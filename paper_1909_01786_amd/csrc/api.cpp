@@ -24,7 +24,7 @@
 #include "train.h"
 
 namespace asp {
-size_t lds_bytes(int threads, int words, int awords, int learning);
+size_t lds_bytes(int threads, int words, int awords, int owords, int learning);
 hipError_t launch_search(const KArgs& a, int threads, int grid, size_t lds, hipStream_t s);
 hipError_t set_max_lds(int threads, size_t lds);
 }  // namespace asp
@@ -82,7 +82,7 @@ bool valid_threads(int t) { return t == 64 || t == 128 || t == 256 || t == 512 |
 // One launch of the search kernel: instances order[first .. first+count),
 // LDS sized for the largest of them.
 struct LaunchClass {
-    int32_t first = 0, count = 0, words = 1, awords = 1, threads = 128;
+    int32_t first = 0, count = 0, words = 1, awords = 1, owords = 0, threads = 128;
     size_t lds = 0;
 };
 
@@ -180,6 +180,9 @@ asp_options default_options() {
     return o;
 }
 
+// LDS a workgroup can hold on gfx950 (static part included).
+constexpr size_t kLdsPerGroup = 160 * 1024 - 1024;
+
 // LDS size classes by variable count (the 2-bit maps take V/4 bytes each).
 std::vector<int64_t> class_bounds(int32_t classes) {
     switch (classes) {
@@ -265,10 +268,11 @@ int32_t make_plan(const std::vector<const HostProgram*>& progs, const asp_option
         LaunchClass lc;
         lc.first = k;
         const int c = cls(P.order[k]);
-        int64_t vmax = 0, amax = 0;
+        int64_t vmax = 0, amax = 0, omax = 0;
         while (k < P.n && cls(P.order[k]) == c) {
             vmax = std::max<int64_t>(vmax, progs[P.order[k]]->V);
             amax = std::max<int64_t>(amax, progs[P.order[k]]->A);
+            omax = std::max<int64_t>(omax, (int64_t)progs[P.order[k]]->A + progs[P.order[k]]->Rh);
             ++k;
         }
         lc.count = k - lc.first;
@@ -276,7 +280,14 @@ int32_t make_plan(const std::vector<const HostProgram*>& progs, const asp_option
         lc.awords = (int32_t)((amax + 1 + 31) / 32);
         const int ci = (int)P.classes.size();
         lc.threads = (class_threads && ci < 4 && class_threads[ci] > 0) ? class_threads[ci] : threads;
-        lc.lds = lds_bytes(lc.threads, lc.words, lc.awords, P.learning);
+        // the learned-occurrence bits (Fwd-learning) only where they fit: a
+        // program that fits the LDS without them is not refused for them
+        lc.owords = P.learning == ASP_LEARN_FWD ? (int32_t)((omax + 1 + 31) / 32) : 0;
+        lc.lds = lds_bytes(lc.threads, lc.words, lc.awords, lc.owords, P.learning);
+        if (lc.lds > kLdsPerGroup) {
+            lc.owords = 0;
+            lc.lds = lds_bytes(lc.threads, lc.words, lc.awords, 0, P.learning);
+        }
         P.classes.push_back(lc);
     }
     uint64_t o = 0;
@@ -392,6 +403,7 @@ KArgs make_args(const Plan& P, uint8_t* arena, int32_t mode, const LaunchClass& 
     a.lookahead = P.lookahead;
     a.words = lc.words;
     a.awords = lc.awords;
+    a.owords = lc.owords;
     a.step_mask = 0;
     a.max_steps = -1;
     a.max_conflicts = -1;

@@ -178,6 +178,9 @@ int encode_program(int32_t n_atoms, int32_t n_rules, const int32_t* head,
                     m.o1 = kLongNogood;   // the nogood's literals: ng_lits[o2 .. o2 + a1)
                     m.o2 = b;
                     m.a1 = e - b;
+                    int32_t* x = &m.n1;   // three of its other literals
+                    for (int32_t q = b, left = 3; left > 0; ++q)
+                        if (q != k) { *x++ = P->ng_lits[q]; --left; }
                 } else {
                     int32_t* o = &m.o1;
                     int32_t* seg = &m.a1;

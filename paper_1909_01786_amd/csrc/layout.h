@@ -22,8 +22,10 @@ constexpr int kAlign = 256;
 // literal, and the nogood's other literals when it has at most three (0
 // pads the unused ones), each with the map segment (start, size) of its
 // complement -- the literal a unit nogood makes true.  A longer nogood has
-// o1 = kLongNogood, o2 = the start of its literals in the nogood CSR and
-// a1 = their count, so that its literals are read right after the entry.
+// o1 = kLongNogood, o2 = the start of its literals in the nogood CSR,
+// a1 = their count, so that its literals are read right after the entry, and
+// n1, a2, n2 = three of its other literals, which decide most visits of one
+// (all of them where the nogood has four literals).
 // A visit of a short nogood is one 32-byte load.
 struct alignas(32) MapEntry {
     int32_t id, self, o1, o2;
@@ -202,6 +204,8 @@ struct KArgs {
     int64_t model_store;         // answer sets kept per instance (n_atoms bytes each)
     int32_t lookahead;           // Decision candidates tried by propagation (<= 1: off)
     int32_t awords;              // LDS words of the 1-bit atom map (this launch's largest A)
+    int32_t owords;              // LDS words of the learned-occurrence bits, 0 without them
+    int32_t pad1;
 };
 
 }  // namespace asp

@@ -50,13 +50,11 @@ constexpr uint32_t NO_ENTRY = 0xffffffffu;      // implier without a map entry (
 constexpr uint64_t FNV_BASIS = 1469598103934665603ull;
 constexpr uint64_t FNV_PRIME = 1099511628211ull;
 constexpr int kMaxWaves = 16;
-constexpr int kFrontCap = 128;   // frontier records kept in LDS (at least; one per thread
-                                 // for wider workgroups)
+constexpr int kFrontCap = 128;   // frontier records, and implication slots (Deps candidate and
+                                 // record), in LDS (at least; one per thread for wider workgroups)
 constexpr int kWinBits = 8;
 constexpr int kWinCap = 1 << kWinBits;   // LDS winner table (variables implied in a round)
 constexpr int kWinProbe = 32;
-constexpr int kImplCap = 128;    // LDS implication slots (Deps candidate and record; at
-                                 // least, one per thread for wider workgroups)
 constexpr uint32_t SLOT_TAG = 0x80000000u;
 constexpr int kLitBatch = 4;     // literals of a long nogood loaded together in a visit
 
@@ -66,6 +64,7 @@ struct Ctl {
     int32_t cdl, qh, qt, n_learned, pend_kind, pending, status, init_done, last_step, pool_top;
     int32_t use_score, consec, dec_open;   // score-driven Decision and its fallback
     int32_t fr_ok;    // the LDS records describe the frontier trail[qh..qt)
+    int32_t fr_big;   // that frontier has more visits than a one-wave round takes
     int32_t epoch;          // resolution-mark epoch (Res-learning)
     int32_t exhausted;      // the search showed no further answer set exists
     int32_t n_pend;         // round conflicts selected for learning (pending, then pend_more)
@@ -84,9 +83,43 @@ struct Scr {
     unsigned long long conf_key;
     unsigned long long conf_key2, conf_thr;   // conflict selection passes
     int32_t tail, clash, changed, pool_top, cap_err, nimpl;
-    int32_t flag[kMaxWaves];
-    int32_t wsum[kMaxWaves + 1];
-    unsigned long long red[kMaxWaves];
+    int32_t wsum[kMaxWaves];       // also what a run of one-wave rounds reports
+    union {                        // (each use begins and ends with a barrier)
+        int32_t flag[kMaxWaves];
+        unsigned long long red[kMaxWaves];
+    };
+    // the arrays of one-wave rounds: the instance's, and the state slot's
+    // with their offsets in units of 256 bytes
+    const MapEntry* ME;
+    const int32_t *NL, *MO;
+    uint8_t* slot;
+    uint32_t o_deps, o_trail, o_lptr, o_ln, o_loff, o_llits, o_pool, o_lvl, o_gpos, o_reason;
+};
+
+#define LDSP __attribute__((address_space(3)))
+#define GLBP __attribute__((address_space(1)))
+
+// LDS arrays of fixed size, as byte offsets from the dynamic LDS base; FC
+// frontier records and implication slots.  The per-instance maps follow.
+template <int FC>
+struct LdsMap {
+    static constexpr uint32_t sB = 0;
+    static constexpr uint32_t tWin = sB + 8 * kMaxW;
+    static constexpr uint32_t iDeps = tWin + 8 * kWinCap;
+    static constexpr uint32_t fDeps = iDeps + 8 * FC;
+    static constexpr uint32_t tKey = fDeps + 8 * FC;
+    static constexpr uint32_t tCode = tKey + 4 * kWinCap;
+    static constexpr uint32_t iS0 = tCode + 4 * kWinCap;
+    static constexpr uint32_t iCs = iS0 + 4 * FC;
+    static constexpr uint32_t iL0 = iCs + 4 * FC;
+    static constexpr uint32_t iCl = iL0 + 4 * FC;
+    static constexpr uint32_t fS0 = iCl + 4 * FC;
+    static constexpr uint32_t fCs = fS0 + 4 * FC;
+    static constexpr uint32_t fL0 = fCs + 4 * FC;
+    static constexpr uint32_t fCl = fL0 + 4 * FC;
+    static constexpr uint32_t fNew = fCl + 4 * FC;
+    static constexpr uint32_t fSlot = fNew + 4 * FC;
+    static constexpr uint32_t end = fSlot + 4 * FC;
 };
 
 struct Ctx {
@@ -104,6 +137,7 @@ struct Ctx {
     int64_t pool_cap;
     uint32_t* pendb;        // 2-bit pending map past the LDS table (workgroup atomics)
     // LDS
+    unsigned char* base;
     uint32_t *valb, *lm;
     int32_t* sOff;
     // frontier records: map segment (start, size) and learned occurrence
@@ -119,12 +153,14 @@ struct Ctx {
     // Deps word of each frontier variable (W = 1), per record; a T-entry
     // buffer (Res-learning's rank tiles)
     unsigned long long *fDeps, *sTile;
+    // Fwd-learning: one bit per literal that can have learned occurrences
+    // (T p of an atom, T b_r of a rule), set when it has some; null without
+    uint32_t* occb;
     int32_t *iS0, *iCs, *iL0, *iCl;
     unsigned long long* sB;
     Scr* scr;
     int32_t W, T, tid, lane, wid, nw;
-    int32_t FC;             // frontier records in LDS: max(T, kFrontCap)
-    int32_t IC;             // implication slots in LDS: max(T, kImplCap)
+    int32_t FC;             // frontier records and implication slots in LDS: max(T, kFrontCap)
     int32_t decision, fallback_after, learning;
     int32_t ext;            // extended search: several answer sets, restarts, activity,
                             // several conflicts learned per step (compile-time in k_search)
@@ -169,6 +205,14 @@ DEV uint32_t lcode(int l) { return l > 0 ? VT : VF; }     // value making litera
 DEV int lvar(int l) { return l < 0 ? -l : l; }
 DEV int lidx(int l) { return 2 * lvar(l) + (l < 0 ? 1 : 0); }
 
+// Index of literal T x among the literals that can have learned occurrences
+// under Fwd-learning: the atoms, then the rules' b_r (-1: neither).
+DEV int occ_bit(int x, int A) {
+    if (x <= A) return x;
+    const int r = x - A - 1, j = r / 3;
+    return r - 3 * j == 0 ? A + 1 + j : -1;
+}
+
 // The lowest-id implier per variable is shared only inside the workgroup:
 // workgroup-scope atomics, ordered by the barriers' workgroup fences.
 DEV unsigned long long ld_wg(const unsigned long long* p) {
@@ -206,6 +250,14 @@ DEV int wave_incl_scan(int x) {
     return x;
 }
 DEV int wave_last(int x) { return __builtin_amdgcn_readlane(x, 63); }
+
+// Number of set bits of a lane mask below this lane.
+DEV int mask_rank(unsigned long long m) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+// Orders one wave's memory accesses for its other lanes (LDS and the L1
+// serve a wave's accesses in order: no instruction, only no reordering).
+DEV void wave_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 
 // Block-wide reductions; every lane must call them.
 DEV unsigned long long block_max_u64(Ctx& c, unsigned long long x) {
@@ -401,6 +453,21 @@ DEV void bind_instance(Ctx& c, Ctl& k, const KArgs& a, int inst) {
     c.resd = (int32_t*)(slot + lay.resd);
     c.act = (int32_t*)(slot + lay.act);
     c.pool_cap = lay.pool_cap;
+    Scr& w = *c.scr;                     // identical from every lane; the caller's barrier follows
+    w.ME = c.ME;
+    w.NL = c.NL;
+    w.MO = c.MO;
+    w.slot = slot;
+    w.o_deps = (uint32_t)(lay.deps >> 8);
+    w.o_trail = (uint32_t)(lay.trail >> 8);
+    w.o_lptr = (uint32_t)(lay.locc_ptr >> 8);
+    w.o_ln = (uint32_t)(lay.locc_n >> 8);
+    w.o_loff = (uint32_t)(lay.l_off >> 8);
+    w.o_llits = (uint32_t)(lay.l_lits >> 8);
+    w.o_pool = (uint32_t)(lay.pool >> 8);
+    w.o_lvl = (uint32_t)(lay.lvl >> 8);
+    w.o_gpos = (uint32_t)(lay.gpos >> 8);
+    w.o_reason = (uint32_t)(lay.reason >> 8);
 }
 
 // Fresh search state: nothing assigned, no learned nogoods.
@@ -408,10 +475,12 @@ DEV void reset_search(Ctx& c, Ctl& k) {
     const int V = k.V, W = c.W, T = c.T, tid = c.tid;
     const int words = (V + 1 + 15) >> 4;
     for (int i = tid; i < words; i += T) {
-        c.valb[i] = 0u;
+        c.valb[i] = i == 0 ? VF : 0u;    // variable 0 (the pad literal) is held false
         pend_zero(c.pendb, i);
     }
     for (int i = tid; i < ((k.A + 1 + 31) >> 5); i += T) c.lm[i] = 0u;
+    if (c.occb)
+        for (int i = tid; i < ((k.A + 1 + k.Rh + 31) >> 5); i += T) c.occb[i] = 0u;
     for (int v = tid; v <= V; v += T) {
         c.lvl[v] = 0;
         c.val8[v] = 0;
@@ -448,7 +517,7 @@ DEV void reset_search(Ctx& c, Ctl& k) {
     k.consec = 0;
     k.dec_open = 0;
     k.t_round = k.t_learn = k.t_decide = k.t_gate = 0;
-    k.fr_ok = 0;
+    k.fr_ok = k.fr_big = 0;
     k.epoch = 0;
     k.exhausted = 0;
     k.n_pend = 0;
@@ -471,9 +540,21 @@ DEV void load_ctrl(Ctx& c, Ctl& k) {
             uint32_t code = x > 0 ? VT : (x < 0 ? VF : 0u);
             wv |= code << (2 * q);
         }
-        c.valb[i] = wv;
+        c.valb[i] = i == 0 ? (wv & ~3u) | VF : wv;
     }
     for (int w = tid; w < c.W; w += T) c.sB[w] = c.ctrl->pend_B[w];
+    if (c.occb) {
+        // bit q: the learned occurrences of T p (p = q <= A) or T b_r
+        const int nb = k.A + 1 + k.Rh;
+        for (int i = tid; i < ((nb + 31) >> 5); i += T) {
+            uint32_t wv = 0u;
+            for (int q = 32 * i; q < 32 * i + 32 && q < nb; ++q) {
+                const int x = q <= k.A ? q : k.A + 3 * (q - k.A - 1) + 1;
+                wv |= c.ln[2 * x] > 0 ? 1u << (q & 31) : 0u;
+            }
+            c.occb[i] = wv;
+        }
+    }
     const SlotCtrl& g = *c.ctrl;
     k.cdl = uni(g.cdl);
     k.qh = uni(g.qh);
@@ -509,7 +590,7 @@ DEV void load_ctrl(Ctx& c, Ctl& k) {
     k.since_restart = uni64(g.since_restart);
     k.steps = 0;
     k.t_round = k.t_learn = k.t_decide = k.t_gate = 0;
-    k.fr_ok = 0;
+    k.fr_ok = k.fr_big = 0;
     tab_clear_all(c);
     bar();
 }
@@ -526,7 +607,7 @@ DEV void flush_counters(Ctx& c, Ctl& k) {
 DEV void save_ctrl(Ctx& c, const Ctl& k) {
     const int V = k.V, T = c.T, tid = c.tid;
     for (int v = tid; v <= V; v += T) {
-        uint32_t code = vget(c.valb, v);
+        uint32_t code = v == 0 ? 0u : vget(c.valb, v);
         c.val8[v] = code == VT ? (int8_t)1 : (code == VF ? (int8_t)-1 : (int8_t)0);
     }
     for (int w = tid; w < c.W; w += T) c.ctrl->pend_B[w] = c.sB[w];
@@ -674,10 +755,20 @@ DEV void visit_one(Ctx& c, const Ctl& k, int id, const MapEntry& e, uint32_t eid
         }
     } else {
         eidx = NO_ENTRY;
+        bool done = false;
         if (id < k.nS) {
-            // a long static nogood: its map entry locates its literals
+            // a long static nogood: its map entry locates its literals, and
+            // holds three of them, which decide most visits
             lits = c.NL + e.o2;
             len = e.a1;
+            const int y[3] = {e.n1, e.a2, e.n2};
+            int op = 0;
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                const uint32_t s = vget(c.valb, lvar(y[j]));
+                op += s == 0u ? 1 : (s != lcode(y[j]) ? 2 : 0);
+            }
+            done = op >= 2;
         } else {
             ng_span(c, k, id, lits, len);
         }
@@ -685,6 +776,7 @@ DEV void visit_one(Ctx& c, const Ctl& k, int id, const MapEntry& e, uint32_t eid
             c.my_visits += 1ull;
             c.my_checks += (unsigned long long)len;
         }
+        if (done) return;
         // from the last literal back, kLitBatch loads in flight: a learned
         // nogood holds its newest literal last, the one most likely to be
         // open or false after a backjump (the outcome -- violated, unit on
@@ -740,9 +832,15 @@ DEV void visit_one(Ctx& c, const Ctl& k, int id, const MapEntry& e, uint32_t eid
                 if (e.o1 != 0 && lvar(e.o1) != x) dA = c.deps[lvar(e.o1)];
                 if (e.o2 != 0 && lvar(e.o2) != x) dB = c.deps[lvar(e.o2)];
             } else {
-                for (int q = 0; q < len; ++q) {
-                    const int y = lvar(lits[q]);
-                    if (y != x) dA |= c.deps[y];
+                for (int q = 0; q < len; q += kLitBatch) {
+                    int y[kLitBatch];
+                    unsigned long long d[kLitBatch];
+#pragma unroll
+                    for (int j = 0; j < kLitBatch; ++j) y[j] = q + j < len ? lvar(lits[q + j]) : 0;
+#pragma unroll
+                    for (int j = 0; j < kLitBatch; ++j) d[j] = y[j] != 0 && y[j] != x ? c.deps[y[j]] : 0ull;
+#pragma unroll
+                    for (int j = 0; j < kLitBatch; ++j) dA |= d[j];
                 }
                 const int li = 2 * x + (code == VF ? 1 : 0);
                 s0 = c.MO[li];
@@ -756,8 +854,8 @@ DEV void visit_one(Ctx& c, const Ctl& k, int id, const MapEntry& e, uint32_t eid
         }
         int first = 0;
         const int t = tab_insert(c, x, first);
-        const int sl = c.W == 1 ? atomicAdd(&c.scr->nimpl, 1) : c.IC;
-        if (sl < c.IC) {
+        const int sl = c.W == 1 ? atomicAdd(&c.scr->nimpl, 1) : c.FC;
+        if (sl < c.FC) {
             if (inl) {
                 s0 = u == e.o1 ? e.a1 : e.a2;
                 s1 = s0 + (u == e.o1 ? e.n1 : e.n2);
@@ -891,28 +989,33 @@ DEV void step_round(Ctx& c, Ctl& k) {
     c.scr->tail = qt;
     c.scr->nimpl = 0;
     bar();
-    visit_pass(c, k, qh, qt, 0);
-    bar();
-    if (uni(c.scr->clash)) {
-        visit_pass(c, k, qh, qt, 1);
-        bar();
-    }
-    // several conflicts learned per step: the next smallest keys, one
-    // selection pass each, on the same snapshot and winners
+    // pass 0 classifies, pass 1 (after a clash) finds the impliers that lost,
+    // pass 2 selects the next conflict, when several are learned per step:
+    // the next smallest keys, one pass each, on the same snapshot and winners
     int nsel = 1;
-    if (c.multi && c.learn_k > 1) {
-        unsigned long long thr = (unsigned long long)uni64((int64_t)c.scr->conf_key);
-        for (int r = 1; r < c.learn_k && thr != ~0ull; ++r) {
-            c.scr->conf_key2 = ~0ull;       // identical from every lane
-            c.scr->conf_thr = thr;
-            bar();
-            visit_pass(c, k, qh, qt, 2);    // ends with a barrier
+    unsigned long long thr = ~0ull;
+#pragma unroll 1
+    for (int pass = 0;;) {
+        visit_pass(c, k, qh, qt, pass);    // ends with a barrier
+        if (pass == 0 && uni(c.scr->clash)) {
+            pass = 1;
+            continue;
+        }
+        if (!c.multi || c.learn_k <= 1) break;
+        if (pass < 2) {
+            thr = (unsigned long long)uni64((int64_t)c.scr->conf_key);
+            pass = 2;
+        } else {
             thr = (unsigned long long)uni64((int64_t)c.scr->conf_key2);
-            bar();                          // every lane has read it
+            bar();                         // every lane has read it
             if (thr == ~0ull) break;
-            k.pend_more[r - 1] = (int32_t)(uint32_t)(thr & 0xffffffffull);
+            k.pend_more[nsel - 1] = (int32_t)(uint32_t)(thr & 0xffffffffull);
             nsel += 1;
         }
+        if (nsel >= c.learn_k || thr == ~0ull) break;
+        c.scr->conf_key2 = ~0ull;          // identical from every lane
+        c.scr->conf_thr = thr;
+        bar();
     }
     const int nt = uni(c.scr->tail);
     // apply every implication, its Deps being the OR of the Deps of the
@@ -1002,6 +1105,7 @@ DEV void step_round(Ctx& c, Ctl& k) {
     k.qh = qt;
     k.qt = nt;
     k.fr_ok = rec ? 1 : 0;
+    k.fr_big = 0;
     k.rounds += 1;
     k.props += nt - qt;
     if (ck != ~0ull) {
@@ -1009,6 +1113,477 @@ DEV void step_round(Ctx& c, Ctl& k) {
         k.pend_kind = 1;
         k.n_pend = nsel;
     }
+}
+
+// Rounds whose visits fit one wave (two per lane): wave 0 runs up to
+// `max_rounds` of them in a row while the other waves wait at one barrier.
+// Most rounds are this small (85-99% have at most 128 visits on the 200-atom
+// programs, the colourings and the batches), and a search is a chain of
+// dependent rounds, so what counts is the latency of one.  Inside one wave
+// nothing has to wait for a barrier: LDS serves a wave's accesses in order.
+//  * The frontier's records stay in registers of the lanes that implied the
+//    variables (two per lane); a scan of their visit counts gives each a run
+//    of visit positions, marked in LDS at its start, and counting the marks
+//    up to a position tells its lane which run it belongs to.
+//  * A one-bit filter over the implied variables (hashed; in the general
+//    round's slot array) finds the rounds that may imply a variable twice;
+//    only those go through the winner table.
+//  * The Deps loads of an implication are waited for one round later, with
+//    the next map entries.
+// Left to the general round: a round of more visits or frontier variables,
+// a full probe window, several conflicts to select from (the run stops
+// before that round, its records back in LDS).  A round's results are those
+// of the general round, bit for bit.  A function of its own, called once per
+// run: its registers are allocated without the search's other state, which
+// cost the loop scratch loads in every round when it was inlined.
+// What bounds it: one wave issues an instruction every four cycles at most,
+// and a round is 600-1000 of them around 0.5-1 us of load latency (6-7
+// thousand cycles on the random batches, 4-5 thousand on the Hamiltonian
+// ones, against 20 thousand and more for the general round of one of them).
+// Per pass, with the general round alone and so: 200-atom programs 2.98 and
+// 1.84 ms, 1024 uneven random programs 394 and 333 ms, 2000 small ones 251
+// and 190 ms, 256 Hamiltonian-cycle programs 133 and 99 ms.
+constexpr int kWaveVisits = 128;
+constexpr int kWaveRun = 256;    // rounds per run (the clock is checked in between)
+constexpr int kWaveLits = 8;     // literals of a long nogood read together
+constexpr int kFilterBits = 8192;
+
+template <int FC, bool RES>
+__device__ __attribute__((noinline)) unsigned wave_run(LDSP Scr* scr_, LDSP unsigned char* base_,
+                                                       uint32_t valb_, uint32_t occ_, int qh, int qt,
+                                                       int A, int nS, int cdl, int max_rounds,
+                                                       int multi) {
+    typedef LdsMap<FC> M;
+    LDSP Scr* s = (LDSP Scr*)(uintptr_t)uni((int)(uintptr_t)scr_);
+    LDSP unsigned char* base = (LDSP unsigned char*)(uintptr_t)uni((int)(uintptr_t)base_);
+    const uint32_t occ = (uint32_t)uni((int)occ_);
+    LDSP uint32_t* valb = (LDSP uint32_t*)(base + uni((int)valb_));
+    LDSP uint32_t* occb = (LDSP uint32_t*)(base + occ);
+    LDSP unsigned long long* tWin = (LDSP unsigned long long*)(base + M::tWin);
+    LDSP unsigned long long* fDeps = (LDSP unsigned long long*)(base + M::fDeps);
+    LDSP uint32_t* filt = (LDSP uint32_t*)(base + M::iDeps);
+    LDSP int32_t* tKey = (LDSP int32_t*)(base + M::tKey);
+    LDSP int32_t* mk = (LDSP int32_t*)(base + M::iS0);    // visit-run marks
+    LDSP int32_t* fS0 = (LDSP int32_t*)(base + M::fS0);
+    LDSP int32_t* fCs = (LDSP int32_t*)(base + M::fCs);
+    LDSP int32_t* fL0 = (LDSP int32_t*)(base + M::fL0);
+    LDSP int32_t* fCl = (LDSP int32_t*)(base + M::fCl);
+    typedef int v4i __attribute__((ext_vector_type(4)));
+    LDSP v4i* run = (LDSP v4i*)(base + M::fS0);           // visit runs, over the records
+    qh = uni(qh);
+    qt = uni(qt);
+    A = uni(A);
+    nS = uni(nS);
+    cdl = uni(cdl);
+    max_rounds = uni(max_rounds);
+    multi = uni(multi);
+    GLBP const v4i* const ME = (GLBP const v4i*)uni64((int64_t)(uintptr_t)s->ME);
+    GLBP const int32_t* const NL = (GLBP const int32_t*)uni64((int64_t)(uintptr_t)s->NL);
+    GLBP const int32_t* const MO = (GLBP const int32_t*)uni64((int64_t)(uintptr_t)s->MO);
+    const uint64_t slot = (uint64_t)uni64((int64_t)(uintptr_t)s->slot);
+    auto arr = [&](uint32_t o) { return slot + ((uint64_t)(uint32_t)uni((int)o) << 8); };
+    GLBP uint64_t* const deps = (GLBP uint64_t*)arr(s->o_deps);
+    GLBP int32_t* const trail = (GLBP int32_t*)arr(s->o_trail);
+    GLBP const int32_t* const lptr = (GLBP const int32_t*)arr(s->o_lptr);
+    GLBP const int32_t* const ln = (GLBP const int32_t*)arr(s->o_ln);
+    GLBP const int32_t* const loff = (GLBP const int32_t*)arr(s->o_loff);
+    GLBP const int32_t* const llits = (GLBP const int32_t*)arr(s->o_llits);
+    GLBP const int32_t* const pool = (GLBP const int32_t*)arr(s->o_pool);
+    GLBP int32_t* const lvl = (GLBP int32_t*)arr(s->o_lvl);
+    GLBP int32_t* const gpos = (GLBP int32_t*)arr(s->o_gpos);
+    GLBP int32_t* const reason = (GLBP int32_t*)arr(s->o_reason);
+    const int lane = threadIdx.x & 63;
+
+    // value field of variable v, and of literal l whether it is false (the
+    // nogood satisfied) or open; the pad literal 0 is neither (variable 0 is
+    // held false)
+    auto field = [&](int v) { return __builtin_amdgcn_ubfe(valb[v >> 4], (v & 15) << 1, 2u); };
+    auto lit_false = [&](int l, uint32_t f) { return (f >> (l > 0 ? 1 : 0)) & 1u; };
+
+    int idx[2], s0[2], se[2], l0[2], cl[2];   // this lane's frontier records
+    int ord[2] = {0, 0};                      // their visit runs
+    int px[2];                                // variables whose Deps are on the way,
+    unsigned long long pd[2], pl[2], pm[2];   // the parts of their OR
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+        const int i = lane + 64 * r;
+        const bool has = i < qt - qh;
+        idx[r] = has ? i : -1;
+        s0[r] = has ? fS0[i] : 0;
+        se[r] = s0[r] + (has ? fCs[i] : 0);
+        l0[r] = has ? fL0[i] : 0;
+        cl[r] = has ? fCl[i] : 0;
+        px[r] = 0;
+        pd[r] = has ? fDeps[i] : 0ull;
+        pl[r] = pm[r] = 0ull;
+    }
+    wave_fence();
+    mk[lane] = mk[lane + 64] = 0;
+#pragma unroll
+    for (int i = 0; i < kFilterBits / 32; i += 64) filt[i + lane] = 0u;
+    s->conf_key = ~0ull;
+    wave_fence();
+    int n = 0, big = 0, visits = 0;
+    unsigned checks = 0u;
+    for (;;) {
+        const int cs0 = se[0] - s0[0], cs1 = se[1] - s0[1];
+        const int cnt0 = cs0 + cl[0], cnt1 = cs1 + cl[1];
+        const int inc = wave_incl_scan(cnt0 + cnt1);
+        const int total = wave_last(inc);
+        if (total > kWaveVisits) {
+            big = 1;
+            break;
+        }
+        if (n == max_rounds) break;
+        // the runs, one after another in lane order: {map entry - position,
+        // first position past the static entries, learned list - position}
+        const int ex0 = inc - cnt0 - cnt1, ex1 = ex0 + cnt0, mark = n + 1;
+        ord[0] = mask_rank(__ballot(cnt0 > 0)) + mask_rank(__ballot(cnt1 > 0));
+        ord[1] = ord[0] + (cnt0 > 0 ? 1 : 0);
+        if (cnt0 > 0) {
+            mk[ex0] = mark;
+            run[ord[0]] = (v4i){s0[0] - ex0, ex0 + cs0, l0[0] - ex0 - cs0, 0};
+        }
+        if (cnt1 > 0) {
+            mk[ex1] = mark;
+            run[ord[1]] = (v4i){s0[1] - ex1, ex1 + cs1, l0[1] - ex1 - cs1, 0};
+        }
+        wave_fence();
+        const int nw2 = total > 64 ? 2 : 1;
+        // each visit's run and map entry (or learned nogood)
+        int ow[2] = {0, 0}, lid[2] = {0, 0};
+        bool act[2], stat[2] = {false, false};
+        v4i eh[2], et[2];          // the entry's two halves
+        eh[0] = eh[1] = et[0] = et[1] = (v4i)(0);
+        int before = -1;
+#pragma unroll
+        for (int w = 0; w < 2; ++w) {
+            const int q = lane + 64 * w;
+            act[w] = q < total;
+            if (w < nw2) {
+                const bool first = mk[q] == mark;
+                const unsigned long long m = __ballot(first);
+                ow[w] = before + mask_rank(m) + (first ? 1 : 0);
+                before += __popcll(m);
+                const v4i rn = run[ow[w]];
+                stat[w] = act[w] && q < rn.y;
+                if (stat[w]) {
+                    GLBP const v4i* p = ME + 2 * (size_t)(uint32_t)(q + rn.x);
+                    eh[w] = p[0];
+                    et[w] = p[1];
+                } else if (act[w]) {
+                    lid[w] = pool[q + rn.z];
+                }
+            }
+        }
+        // the Deps of the frontier: of the variables this lane implied a
+        // round ago (or brought into the run)
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            const unsigned long long d = pd[r] | pl[r] | pm[r];
+            if ((r ? cnt1 : cnt0) > 0) fDeps[ord[r]] = d;
+            if (px[r] != 0) deps[px[r]] = d;
+        }
+        wave_fence();
+        // classify the short nogoods: {id, self, o1, o2}, {a1, n1, a2, n2}
+        int open[2] = {2, 2}, len[2] = {0, 0}, id[2], u[2] = {0, 0};
+        int ns0[2] = {0, 0}, nse[2] = {0, 0};
+        unsigned long long nd[2] = {0ull, 0ull}, nl[2] = {0ull, 0ull}, nm[2] = {0ull, 0ull};
+        bool lng[2] = {false, false};
+#pragma unroll
+        for (int w = 0; w < 2; ++w) {
+            id[w] = stat[w] ? eh[w].x : lid[w];
+            if (w >= nw2) continue;
+            const int o1 = eh[w].z, o2 = eh[w].w;
+            lng[w] = act[w] && (!stat[w] || o1 == kLongNogood);
+            if (act[w] && !lng[w]) {
+                const uint32_t f1 = field(lvar(o1)), f2 = field(lvar(o2));
+                const bool p1 = f1 == 0u, p2 = f2 == 0u;
+                len[w] = 1 + (o1 != 0 ? 1 : 0) + (o2 != 0 ? 1 : 0);
+                open[w] = (p1 ? 1 : 0) + (p2 ? 1 : 0);
+                if (lit_false(o1, f1) | lit_false(o2, f2)) open[w] = 2;
+                u[w] = p1 ? o1 : o2;
+                ns0[w] = p1 ? et[w].x : et[w].z;
+                nse[w] = ns0[w] + (p1 ? et[w].y : et[w].w);
+                if (open[w] == 1) {
+                    nd[w] = fDeps[ow[w]];
+                    nl[w] = deps[lvar(p1 ? o2 : o1)];   // variable 0 has none
+                }
+            }
+        }
+        // Long and learned nogoods.  Three of a long static nogood's other
+        // literals come with the entry and decide most of them (all those of
+        // four literals); else they are read from the last back (a learned
+        // nogood's newest literal, the likeliest to be open or false after a
+        // backjump, is its last), kWaveLits loads in flight.
+        if (__ballot(lng[0] || lng[1]) != 0ull) {
+#pragma unroll 1
+            for (int w = 0; w < nw2; ++w) {
+                if (!(w ? lng[1] : lng[0])) continue;
+                const int nid = w ? id[1] : id[0];
+                int y1 = w ? et[1].y : et[0].y, y2 = w ? et[1].z : et[0].z,
+                    y3 = w ? et[1].w : et[0].w;
+                GLBP const int32_t* lits;
+                int m, op = 0, uu = 0;
+                bool all = true;             // decided by the entry's literals
+                auto see = [&](int l) {
+                    const uint32_t f = field(lvar(l));
+                    if (lit_false(l, f)) op += 8;
+                    if (f == 0u) {
+                        op += 1;
+                        uu = l;
+                    }
+                };
+                if (w ? stat[1] : stat[0]) {
+                    lits = NL + (w ? eh[1].w : eh[0].w);
+                    m = w ? et[1].x : et[0].x;
+                    see(y1);
+                    see(y2);
+                    see(y3);
+                    all = m == 4 || op >= 2;
+                } else {
+                    const int o = loff[nid - nS];
+                    lits = llits + o;
+                    m = loff[nid - nS + 1] - o;
+                    all = false;
+                }
+                if (!all) {
+                    op = 0;
+                    for (int q = m; q > 0 && op < 2; q -= kWaveLits) {
+                        int l[kWaveLits];
+#pragma unroll
+                        for (int j = 0; j < kWaveLits; ++j) l[j] = lits[q - 1 - j > 0 ? q - 1 - j : 0];
+#pragma unroll
+                        for (int j = 0; j < kWaveLits; ++j) see(j < q ? l[j] : 0);
+                    }
+                }
+                unsigned long long own = 0ull, ac = 0ull, bc = 0ull;
+                int a0 = 0, an = 0;
+                if (op == 1) {
+                    const int li = lidx(-uu);
+                    a0 = MO[li];
+                    an = MO[li + 1];
+                    if (all) {
+                        // the visit's own literal, and the two of three that are not open
+                        if (y3 == uu) y3 = y1;
+                        else if (y2 == uu) y2 = y1;
+                        own = fDeps[w ? ow[1] : ow[0]];
+                        ac = deps[lvar(y2)];
+                        bc = deps[lvar(y3)];
+                    } else {
+                        for (int q = m; q > 0; q -= kLitBatch) {
+                            int l[kLitBatch];
+#pragma unroll
+                            for (int j = 0; j < kLitBatch; ++j) l[j] = lits[q - 1 - j > 0 ? q - 1 - j : 0];
+                            unsigned long long d[kLitBatch];
+#pragma unroll
+                            for (int j = 0; j < kLitBatch; ++j) d[j] = deps[l[j] == uu ? 0 : lvar(l[j])];
+#pragma unroll
+                            for (int j = 0; j < kLitBatch; ++j) ac |= d[j];
+                        }
+                    }
+                }
+                if (w) {
+                    open[1] = op; len[1] = m; u[1] = uu; ns0[1] = a0; nse[1] = an;
+                    nd[1] = own; nl[1] = ac; nm[1] = bc;
+                } else {
+                    open[0] = op; len[0] = m; u[0] = uu; ns0[0] = a0; nse[0] = an;
+                    nd[0] = own; nl[0] = ac; nm[0] = bc;
+                }
+            }
+        }
+        bool unit[2];
+        int x[2];
+        uint32_t old[2], bit[2];
+#pragma unroll
+        for (int w = 0; w < 2; ++w) {
+            unit[w] = act[w] && open[w] == 1;
+            x[w] = lvar(u[w]);
+            bit[w] = 1u << (x[w] & 31);
+            old[w] = 0u;
+            if (unit[w])
+                old[w] = __hip_atomic_fetch_or(&filt[(x[w] & (kFilterBits - 1)) >> 5], bit[w],
+                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+        unsigned long long ub0 = __ballot(unit[0]), ub1 = __ballot(unit[1]);
+        bool conf[2] = {act[0] && open[0] == 0, act[1] && open[1] == 0};
+        bool any_conf = __ballot(conf[0] || conf[1]) != 0ull;
+        const bool twice = __ballot((old[0] & bit[0]) != 0u || (old[1] & bit[1]) != 0u) != 0ull;
+#pragma unroll
+        for (int w = 0; w < 2; ++w)
+            if (unit[w]) filt[(x[w] & (kFilterBits - 1)) >> 5] = 0u;
+        int stop = 0;
+        if (twice) {
+            // a variable may have two impliers: the lowest nogood id wins (the
+            // visit breaks the tie of a nogood reached by two literals), one
+            // of the other value is a conflict
+            unsigned long long key[2];
+            int t[2] = {-1, -1};
+#pragma unroll 1
+            for (int w = 0; w < nw2; ++w) {
+                if (!(w ? unit[1] : unit[0])) continue;
+                const int xw = w ? x[1] : x[0];
+                int at = -1;
+                for (int p = 0; p < kWinProbe; ++p) {
+                    const int sl = (tab_hash(xw) + p) & (kWinCap - 1);
+                    int32_t was = -1;
+                    __hip_atomic_compare_exchange_strong(&tKey[sl], &was, xw, __ATOMIC_RELAXED,
+                                                         __ATOMIC_RELAXED,
+                                                         __HIP_MEMORY_SCOPE_WORKGROUP);
+                    if (was == -1 || was == xw) {
+                        at = sl;
+                        break;
+                    }
+                }
+                if (w) t[1] = at; else t[0] = at;
+            }
+            stop = __ballot((unit[0] && t[0] < 0) || (unit[1] && t[1] < 0)) != 0ull ? 1 : 0;
+#pragma unroll
+            for (int w = 0; w < 2; ++w) {
+                key[w] = ((unsigned long long)(uint32_t)(id[w] * 2 + (u[w] > 0 ? 1 : 0)) << 32) |
+                         (uint32_t)(lane + 64 * w);
+                if (t[w] >= 0)
+                    __hip_atomic_fetch_min(&tWin[t[w]], key[w], __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
+            wave_fence();
+            unsigned long long wk[2];
+#pragma unroll
+            for (int w = 0; w < 2; ++w) wk[w] = t[w] >= 0 ? tWin[t[w]] : key[w];
+            wave_fence();
+#pragma unroll
+            for (int w = 0; w < 2; ++w) {
+                if (t[w] >= 0) {
+                    tWin[t[w]] = WIN_NONE;
+                    tKey[t[w]] = -1;
+                }
+                conf[w] = conf[w] || (unit[w] && ((wk[w] ^ key[w]) >> 32 & 1ull) != 0ull);
+                unit[w] = unit[w] && wk[w] == key[w];
+            }
+            any_conf = __ballot(conf[0] || conf[1]) != 0ull;
+            ub0 = __ballot(unit[0]);
+            ub1 = __ballot(unit[1]);
+        }
+        if (stop || (any_conf && multi)) {
+            big = 1;                   // the general round does this one
+            break;
+        }
+        if (any_conf) {
+#pragma unroll
+            for (int w = 0; w < 2; ++w)
+                if (conf[w])
+                    __hip_atomic_fetch_min(&s->conf_key,
+                                           ((unsigned long long)(uint32_t)len[w] << 32) | (uint32_t)id[w],
+                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+        // apply: the implied variables, in visit order, become the frontier
+        const int n0 = __popcll(ub0);
+        const int rk[2] = {mask_rank(ub0), n0 + mask_rank(ub1)};
+#pragma unroll
+        for (int w = 0; w < 2; ++w) {
+            checks += (unsigned)len[w];
+            px[w] = unit[w] ? x[w] : 0;
+            idx[w] = unit[w] ? rk[w] : -1;
+            s0[w] = unit[w] ? ns0[w] : 0;
+            se[w] = unit[w] ? nse[w] : 0;
+            l0[w] = cl[w] = 0;
+            pd[w] = nd[w];
+            pl[w] = nl[w];
+            pm[w] = nm[w];
+            if (unit[w]) {
+                const bool pos = u[w] < 0;      // the literal made true is -u
+                __hip_atomic_fetch_or(&valb[x[w] >> 4], (pos ? VT : VF) << ((x[w] & 15) << 1),
+                                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                trail[qt + rk[w]] = x[w];
+                if (RES) {
+                    lvl[x[w]] = cdl;
+                    gpos[x[w]] = qt;
+                    reason[x[w]] = id[w];
+                }
+                bool has = true;       // may the new literal have learned occurrences?
+                if (!RES) {
+                    const int b = pos ? occ_bit(x[w], A) : -1;
+                    has = b >= 0 && (occ == 0u || ((occb[b >> 5] >> (b & 31)) & 1u));
+                }
+                if (has) {
+                    const int li = 2 * x[w] + (pos ? 0 : 1);
+                    l0[w] = lptr[li];
+                    cl[w] = ln[li];
+                }
+            }
+        }
+        visits += total;
+        qh = qt;
+        qt += n0 + __popcll(ub1);
+        n += 1;
+        if (any_conf || qt == qh) break;
+        wave_fence();
+    }
+    wave_fence();
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+        if (idx[r] >= 0) {
+            const unsigned long long d = pd[r] | pl[r] | pm[r];
+            fS0[idx[r]] = s0[r];
+            fCs[idx[r]] = se[r] - s0[r];
+            fL0[idx[r]] = l0[r];
+            fCl[idx[r]] = cl[r];
+            fDeps[idx[r]] = d;
+            if (px[r] != 0) deps[px[r]] = d;
+        }
+    s->wsum[0] = n;                    // identical from the wave's lanes
+    s->wsum[1] = qh;
+    s->wsum[2] = qt;
+    s->wsum[3] = big;
+    s->wsum[4] = visits;
+    return checks;
+}
+
+template <int FC>
+DEV int wave_rounds(Ctx& c, Ctl& k, int max_rounds) {
+    if (uni(c.wid) == 0) {
+        LDSP unsigned char* base = (LDSP unsigned char*)c.base;
+        const uint32_t vo = (uint32_t)((unsigned char*)c.valb - c.base);
+        const uint32_t oo = c.occb ? (uint32_t)((unsigned char*)c.occb - c.base) : 0u;
+        const int multi = c.multi && c.learn_k > 1 ? 1 : 0;
+        const unsigned ch = c.learning == LEARN_RES
+            ? wave_run<FC, true>((LDSP Scr*)c.scr, base, vo, oo, k.qh, k.qt, k.A, k.nS, k.cdl, max_rounds, multi)
+            : wave_run<FC, false>((LDSP Scr*)c.scr, base, vo, oo, k.qh, k.qt, k.A, k.nS, k.cdl, max_rounds, multi);
+        c.my_checks += (unsigned long long)ch;
+    }
+    bar();
+    const int n = uni(c.scr->wsum[0]);
+    const int qt = uni(c.scr->wsum[2]);
+    c.my_visits += c.tid == 0 ? (unsigned long long)c.scr->wsum[4] : 0ull;
+    k.rounds += n;
+    k.props += qt - k.qt;
+    k.qh = uni(c.scr->wsum[1]);
+    k.qt = qt;
+    k.fr_big = uni(c.scr->wsum[3]);
+    const unsigned long long ck = (unsigned long long)uni64((int64_t)c.scr->conf_key);
+    if (ck != ~0ull) {
+        k.pending = (int32_t)(uint32_t)(ck & 0xffffffffull);
+        k.pend_kind = 1;
+        k.n_pend = 1;
+    }
+    return n;
+}
+
+// Up to max_rounds rounds from the current frontier; returns how many.
+DEV int step_rounds(Ctx& c, Ctl& k, int max_rounds) {
+    if (c.W == 1 && k.fr_ok && !k.fr_big && k.qt - k.qh <= kWaveVisits) {
+        int n;
+        switch (c.FC) {
+        case 128: n = wave_rounds<128>(c, k, max_rounds); break;
+        case 256: n = wave_rounds<256>(c, k, max_rounds); break;
+        case 512: n = wave_rounds<512>(c, k, max_rounds); break;
+        default: n = wave_rounds<1024>(c, k, max_rounds); break;
+        }
+        if (n > 0) return n;
+        bar();                             // every wave has read the report
+    }
+    step_round(c, k);
+    return 1;
 }
 
 // Res-learning (Alg. 3) of round conflict `conf` at level `top`,
@@ -1178,9 +1753,14 @@ DEV int res_learn(Ctx& c, Ctl& k, const KArgs& a, int conf, int base, int top, i
 // Literal occurrence lists of a new learned nogood llits[base..base+nN)
 // (one lane per literal; the literals are distinct): doubling arrays in the
 // slot's pool, claimed from scr->pool_top; an overflow sets scr->cap_err.
-DEV void add_occurrences(Ctx& c, int base, int nN, int newid) {
+DEV void add_occurrences(Ctx& c, int A, int base, int nN, int newid) {
     for (int i = c.tid; i < nN; i += c.T) {
-        int li = lidx(c.llits[base + i]);
+        const int l = c.llits[base + i];
+        int li = lidx(l);
+        if (c.occb && l > 0) {
+            const int b = occ_bit(l, A);
+            if (b >= 0) atomicOr(&c.occb[b >> 5], 1u << (b & 31));
+        }
         int n = c.ln[li], cap = c.lcap[li], p = c.lptr[li];
         if (n == cap) {
             int ncap = cap ? 2 * cap : 4;
@@ -1204,7 +1784,7 @@ DEV void add_occurrences(Ctx& c, int base, int nN, int newid) {
 DEV void restart(Ctx& c, Ctl& k) {
     const int W = c.W, T = c.T, tid = c.tid;
     const int words = (k.V + 1 + 15) >> 4;
-    for (int i = tid; i < words; i += T) c.valb[i] = 0u;
+    for (int i = tid; i < words; i += T) c.valb[i] = i == 0 ? VF : 0u;
     for (int i = tid; i < k.qt; i += T) {
         const int v = c.trail[i];
         if (c.learning == LEARN_RES) c.lvl[v] = 0;
@@ -1417,7 +1997,7 @@ DEV void step_learn(Ctx& c, Ctl& k, const KArgs& a) {
         k.hash = fnv(k.hash, ibj);
         c.loff[k.n_learned + 1] = ibase + inN;
         bar();
-        add_occurrences(c, ibase, inN, iid);
+        add_occurrences(c, k.A, ibase, inN, iid);
         k.n_learned += 1;
         k.learned_lits += inN;
         k.learned += 1;
@@ -1499,6 +2079,7 @@ DEV void step_learn(Ctx& c, Ctl& k, const KArgs& a) {
     k.qh = start;
     k.qt = start + 1;
     k.fr_ok = 1;
+    k.fr_big = 0;
     k.pending = -1;
     k.pend_kind = 0;
     k.n_pend = 0;
@@ -1617,6 +2198,7 @@ DEV void decide_rule(Ctx& c, Ctl& k, int j) {
     k.qh = k.qt;
     k.qt = k.qt + 1;
     k.fr_ok = 1;
+    k.fr_big = 0;
 }
 
 DEV int rule_of(unsigned long long key) { return (int)(0xffffffffu - (uint32_t)(key & 0xffffffffull)); }
@@ -1653,7 +2235,7 @@ DEV void lookahead_decide(Ctx& c, Ctl& k, unsigned long long best, const int32_t
             decide_rule(c, k, j);
             k.dec_open = 1;
             while (k.qt > k.qh && !k.pend_kind && k.status == ST_RUNNING) {
-                step_round(c, k);
+                step_rounds(c, k, kWaveRun);
                 bar();
             }
             if (k.pend_kind || k.qt == k.V || k.status != ST_RUNNING) {
@@ -1802,7 +2384,7 @@ DEV void answer_set(Ctx& c, Ctl& k, const KArgs& a) {
     c.scr->pool_top = k.pool_top;
     c.scr->cap_err = 0;
     bar();
-    add_occurrences(c, base, nN, newid);
+    add_occurrences(c, A, base, nN, newid);
     bar();
     k.pool_top = uni(c.scr->pool_top);
     if (uni(c.scr->cap_err)) {
@@ -1894,6 +2476,7 @@ DEV void step_gate(Ctx& c, Ctl& k, const KArgs& a, uint8_t* model) {
 // Run the state machine until the search ends, the step budget is used, or
 // the next step is not allowed (step kernels).
 DEV void run_search(Ctx& c, Ctl& k, const KArgs& a, uint8_t* model, uint64_t t0) {
+    int64_t next_clock = 0;
     for (;;) {
         {
             // The thread index passes through an empty asm statement at each
@@ -1914,9 +2497,10 @@ DEV void run_search(Ctx& c, Ctl& k, const KArgs& a, uint8_t* model, uint64_t t0)
             } else if (a.max_steps >= 0 && k.steps >= a.max_steps) {
                 k.status = ST_E_INTERNAL;
             }
-            // the clock is read per wave, every 64 steps; the workgroup
-            // acts on the OR
-            if ((k.steps & 63) == 0) {
+            // the clock is read per wave, every 64 steps (or run of rounds);
+            // the workgroup acts on the OR
+            if (k.steps >= next_clock) {
+                next_clock = k.steps + 64;
                 int late = (a.max_ticks && (uint64_t)(wall_clock64() - t0) > a.max_ticks) ? 1 : 0;
                 if (block_any(c, late)) k.status = ST_E_TIMEOUT;
             }
@@ -1938,9 +2522,15 @@ DEV void run_search(Ctx& c, Ctl& k, const KArgs& a, uint8_t* model, uint64_t t0)
         kind = uni(kind);
         if (kind == STEP_DONE) break;
         const uint64_t ts = wall_clock64();
+        int done = 1;                      // steps (rounds) this turn does
         switch (kind) {
         case STEP_INIT: step_init(c, k); break;
-        case STEP_ROUND: step_round(c, k); break;
+        case STEP_ROUND: {
+            int most = kWaveRun;
+            if (a.max_steps >= 0 && a.max_steps - k.steps < most) most = (int)(a.max_steps - k.steps);
+            done = step_rounds(c, k, uni(most));
+            break;
+        }
         case STEP_LEARN: step_learn(c, k, a); break;
         case STEP_GATE: step_gate(c, k, a, model); break;
         default: kind = step_decide_or_complete(c, k); break;
@@ -1950,7 +2540,7 @@ DEV void run_search(Ctx& c, Ctl& k, const KArgs& a, uint8_t* model, uint64_t t0)
         else if (kind == STEP_LEARN) k.t_learn += dt;
         else if (kind == STEP_GATE) k.t_gate += dt;
         else k.t_decide += dt;
-        k.steps += 1;
+        k.steps += done;
         k.last_step = kind;
         if ((k.status == ST_UNSAT || k.status == ST_UNKNOWN) && k.models > 0) {
             // the search ended after answer sets were found
@@ -2002,7 +2592,7 @@ DEV void write_result(Ctx& c, const Ctl& k, const KArgs& a, uint64_t t0) {
 // carries only its own code and registers.
 template <int MAXT, int LR, int EN>
 __global__ __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu((EN == 0 && LR == 0) ? 4 : 3))) void k_search(KArgs a) {
-    HIP_DYNAMIC_SHARED(unsigned long long, smem64);  // 8-byte aligned base
+    HIP_DYNAMIC_SHARED(uint4, smem16);     // 16-byte aligned base
     __shared__ Scr scr;
     Ctx c;
     Ctl k;
@@ -2020,70 +2610,65 @@ __global__ __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu((EN == 0 &
     c.wid = threadIdx.x >> 6;
     c.nw = MAXT / 64;
     c.FC = MAXT > kFrontCap ? MAXT : kFrontCap;
-    c.IC = MAXT > kImplCap ? MAXT : kImplCap;
     c.scr = &scr;
     c.my_visits = c.my_checks = 0ull;
     {
-        // 8-byte arrays first (the base is 8-byte aligned), then 4-byte ones
-        unsigned char* p = (unsigned char*)smem64;
-        c.sB = (unsigned long long*)p; p += sizeof(unsigned long long) * kMaxW;
-        c.tWin = (unsigned long long*)p; p += sizeof(unsigned long long) * kWinCap;
-        c.iDeps = (unsigned long long*)p; p += sizeof(unsigned long long) * c.IC;
-        c.fDeps = (unsigned long long*)p; p += sizeof(unsigned long long) * c.FC;
+        typedef LdsMap<(MAXT > kFrontCap ? MAXT : kFrontCap)> M;
+        unsigned char* p = (unsigned char*)smem16;
+        c.base = p;
+        c.sB = (unsigned long long*)(p + M::sB);
+        c.tWin = (unsigned long long*)(p + M::tWin);
+        c.iDeps = (unsigned long long*)(p + M::iDeps);
+        c.fDeps = (unsigned long long*)(p + M::fDeps);
+        c.tKey = (int32_t*)(p + M::tKey);
+        c.tCode = (int32_t*)(p + M::tCode);
+        c.iS0 = (int32_t*)(p + M::iS0);
+        c.iCs = (int32_t*)(p + M::iCs);
+        c.iL0 = (int32_t*)(p + M::iL0);
+        c.iCl = (int32_t*)(p + M::iCl);
+        c.fS0 = (int32_t*)(p + M::fS0);
+        c.fCs = (int32_t*)(p + M::fCs);
+        c.fL0 = (int32_t*)(p + M::fL0);
+        c.fCl = (int32_t*)(p + M::fCl);
+        c.fNew = (int32_t*)(p + M::fNew);
+        c.fSlot = (int32_t*)(p + M::fSlot);
+        p += M::end;
         c.sTile = nullptr;   // Res-learning only
         if (LR == LEARN_RES) {
             c.sTile = (unsigned long long*)p;
             p += sizeof(unsigned long long) * MAXT;
         }
+        c.sOff = (int32_t*)p; p += sizeof(int32_t) * MAXT;
         c.valb = (uint32_t*)p; p += sizeof(uint32_t) * a.words;
         c.lm = (uint32_t*)p; p += sizeof(uint32_t) * a.awords;
-        c.tKey = (int32_t*)p; p += sizeof(int32_t) * kWinCap;
-        c.tCode = (int32_t*)p; p += sizeof(int32_t) * kWinCap;
-        c.iS0 = (int32_t*)p; p += sizeof(int32_t) * c.IC;
-        c.iCs = (int32_t*)p; p += sizeof(int32_t) * c.IC;
-        c.iL0 = (int32_t*)p; p += sizeof(int32_t) * c.IC;
-        c.iCl = (int32_t*)p; p += sizeof(int32_t) * c.IC;
-        c.sOff = (int32_t*)p; p += sizeof(int32_t) * MAXT;
-        c.fS0 = (int32_t*)p; p += sizeof(int32_t) * c.FC;
-        c.fCs = (int32_t*)p; p += sizeof(int32_t) * c.FC;
-        c.fL0 = (int32_t*)p; p += sizeof(int32_t) * c.FC;
-        c.fCl = (int32_t*)p; p += sizeof(int32_t) * c.FC;
-        c.fNew = (int32_t*)p; p += sizeof(int32_t) * c.FC;
-        c.fSlot = (int32_t*)p; p += sizeof(int32_t) * c.FC;
+        // Fwd-learning, where LDS has room for it
+        c.occb = LR != LEARN_RES && a.owords > 0 ? (uint32_t*)p : nullptr;
     }
     const uint64_t t0 = wall_clock64();
+    int inst = 0;
     if (a.mode == MODE_SOLVE) {
         // one workgroup per instance; the hardware dispatcher keeps as many
         // resident as LDS and wave slots allow
         if ((int)blockIdx.x >= a.count) return;
-        const int inst = uni(a.order[a.first + (int)blockIdx.x]);
-        bind_instance(c, k, a, inst);
-        reset_search(c, k);
-        run_search(c, k, a, a.models + a.inst[inst].model, t0);
-        flush_counters(c, k);
-        write_result(c, k, a, t0);
-        save_ctrl(c, k);
-    } else {
-        bind_instance(c, k, a, 0);
-        if (a.mode == MODE_STEPS) {
-            load_ctrl(c, k);
-            run_search(c, k, a, a.models + a.inst[0].model, t0);
-        } else {
-            reset_search(c, k);
-        }
-        flush_counters(c, k);
-        save_ctrl(c, k);
+        inst = uni(a.order[a.first + (int)blockIdx.x]);
     }
+    bind_instance(c, k, a, inst);
+    if (a.mode == MODE_STEPS) load_ctrl(c, k);
+    else reset_search(c, k);
+    if (a.mode != MODE_RESET) run_search(c, k, a, a.models + a.inst[inst].model, t0);
+    flush_counters(c, k);
+    if (a.mode == MODE_SOLVE) write_result(c, k, a, t0);
+    save_ctrl(c, k);
 }
 
 // ------------------------------------------------------------ launchers
-size_t lds_bytes(int threads, int words, int awords, int learning) {
+size_t lds_bytes(int threads, int words, int awords, int owords, int learning) {
     const size_t fc = threads > kFrontCap ? (size_t)threads : (size_t)kFrontCap;
-    const size_t ic = threads > kImplCap ? (size_t)threads : (size_t)kImplCap;
-    return sizeof(uint32_t) * ((size_t)words + (size_t)awords) + sizeof(unsigned long long) * kMaxW +
+    return sizeof(uint32_t) * ((size_t)words + (size_t)awords + (size_t)owords) +
+           sizeof(unsigned long long) * kMaxW +
            sizeof(int32_t) * (size_t)threads + sizeof(int32_t) * 6 * fc +
            (sizeof(unsigned long long) + 2 * sizeof(int32_t)) * (size_t)kWinCap +
-           (sizeof(unsigned long long) + 4 * sizeof(int32_t)) * ic +
+           (sizeof(unsigned long long) + 4 * sizeof(int32_t)) * fc +
            sizeof(unsigned long long) * (fc + (learning == LEARN_RES ? (size_t)threads : 0));
 }
 

@@ -1,0 +1,74 @@
+"""Runs of one-wave rounds at their edges, against the oracle.
+
+A run takes the rounds whose visits fit one wave (two per lane) and leaves
+the others to the general round; single steps never start one (the frontier
+records are in LDS only between the steps of one launch), so each program is
+run from the start for n steps at once and the whole state is compared.
+"""
+import pytest
+import torch  # noqa: F401  (loads the HIP runtime the library uses)
+
+import aspgen
+import oracle
+from parity import STATUS, assert_same_state, assert_same_stats
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def P():
+    assert torch.cuda.is_available(), "GPU tests need a HIP device"
+    import paper_1909_01786_amd as P
+    P.lib()
+    return P
+
+
+def fan(width, per_atom):
+    """`width` atoms that all follow from one choice, each with `per_atom`
+    rules (support nogoods of per_atom + 1 literals), and a second layer
+    needing two of them, so that one round implies many variables, some of
+    them twice."""
+    rules = [(1, [-2]), (2, [-1])]
+    for i in range(width):
+        a = 3 + i
+        rules += [(a, [1])] + [(a, [2, -(3 + (i + 1 + j) % width)]) for j in range(per_atom - 1)]
+        rules.append((3 + width + i // 2, [a, 3 + (i + 1) % width]))
+    return aspgen.from_rules(3 + width + width // 2, rules, f"fan{width}_{per_atom}")
+
+
+def _compare(P, prog, n, threads, **kw):
+    o = oracle.Solver(prog, learning=kw.get("learning", 0))
+    for _ in range(n):
+        if o.next_step() == oracle.ST_DONE:
+            return False
+        o.step()
+    g = P.Program(prog, **kw).bind("cuda", threads=threads)
+    rc, st = g.run_steps(n, P.limits(-1, 30000))
+    s = o.state()
+    assert rc == STATUS[s.status], (prog.name, n)
+    if s.status == oracle.RUNNING:
+        assert_same_state(s, g.export_state(), (prog.name, n))
+    assert_same_stats(o.stats(), st, (prog.name, n))
+    return True
+
+
+@pytest.mark.parametrize("threads", [64, 128, 256])
+@pytest.mark.parametrize("width,per_atom", [(1, 1), (20, 3), (21, 4), (22, 7), (31, 2), (32, 8),
+                                            (43, 1), (63, 1), (64, 1), (65, 3), (127, 1), (129, 2),
+                                            (16, 9), (9, 17)])
+def test_round_edges(P, width, per_atom, threads):
+    """Frontiers and visit counts around one and two per lane, and nogoods of
+    2 to 18 literals, after every number of steps up to 40."""
+    prog = fan(width, per_atom)
+    for n in range(1, 41):
+        if not _compare(P, prog, n, threads):
+            break
+
+
+@pytest.mark.parametrize("learning", [0, 1])
+@pytest.mark.parametrize("seed", range(6))
+def test_learned_visits(P, seed, learning):
+    """Searches with learned nogoods: the state after 50, 200, 400 steps."""
+    for prog in (aspgen.single_random(1000 + seed), aspgen.batch_hamiltonian(seed, n_lo=20, n_hi=30)):
+        for n in (50, 200, 400):
+            _compare(P, prog, n, 128, learning=learning)
