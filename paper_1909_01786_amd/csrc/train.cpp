@@ -25,6 +25,7 @@ namespace {
 
 constexpr int H = ASP_SCORER_H, F = ASP_SCORER_F, L = ASP_SCORER_L;
 constexpr int64_t HH = (int64_t)H * H;
+constexpr int kMaxSteps = 100000;     // steps per call (the losses are kept on the device)
 
 // Offsets (floats) of each parameter group in the flat vector.
 struct ParamLayout {
@@ -89,7 +90,7 @@ Sizes sizes_of(const std::vector<const HostProgram*>& progs) {
 
 struct WsLayout {
     uint64_t P, G, M, V, range, lim, loss, Xv, Xc, coff, cidx, voff, vidx, cscale, vscale, y;
-    uint64_t Av[L + 1], Ac[L + 1], tv[3], tc[3], dv[2], dc[2];
+    uint64_t Av[L + 1], Ac[L + 1], Bv[L + 1], Bc[L + 1], gv, gc, part;
     uint64_t total;
 };
 
@@ -108,7 +109,8 @@ WsLayout ws_layout(const Sizes& z) {
     W.V = take(4 * PL.n);
     W.range = take(PL.n);
     W.lim = take(4 * 4);
-    W.loss = take(4 * 4);
+    W.loss = take(4 * (uint64_t)kMaxSteps);
+    W.part = take(4 * (uint64_t)kTrParts * kTrPart);
     W.Xv = take(4 * F * z.nv);
     W.Xc = take(4 * F * z.nc);
     W.coff = take(8 * (z.nc + 1));
@@ -120,10 +122,10 @@ WsLayout ws_layout(const Sizes& z) {
     W.y = take(4 * z.nv);
     for (int l = 0; l <= L; ++l) W.Av[l] = take(4 * H * z.nv);
     for (int l = 0; l <= L; ++l) W.Ac[l] = take(4 * H * z.nc);
-    for (int i = 0; i < 3; ++i) W.tv[i] = take(4 * H * z.nv);
-    for (int i = 0; i < 3; ++i) W.tc[i] = take(4 * H * z.nc);
-    for (int i = 0; i < 2; ++i) W.dv[i] = take(4 * H * z.nv);
-    for (int i = 0; i < 2; ++i) W.dc[i] = take(4 * H * z.nc);
+    for (int l = 0; l <= L; ++l) W.Bv[l] = take(2 * H * z.nv);   // bfloat16 copies
+    for (int l = 0; l <= L; ++l) W.Bc[l] = take(2 * H * z.nc);
+    W.gv = take(4 * H * z.nv);
+    W.gc = take(4 * H * z.nc);
     W.total = o;
     return W;
 }
@@ -327,6 +329,7 @@ int32_t train_run(const std::vector<const HostProgram*>& progs, const float* lab
     TRCHK(hipStreamSynchronize(s));   // host staging vectors die here
 
     auto F32 = [&](uint64_t off) { return (float*)(ws + off); };
+    auto B16 = [&](uint64_t off) { return (uint16_t*)(ws + off); };
     float* Pp = F32(W.P);
     float* Gp = F32(W.G);
     const int64_t* c_off = (const int64_t*)(ws + W.coff);
@@ -337,69 +340,59 @@ int32_t train_run(const std::vector<const HostProgram*>& progs, const float* lab
     const float* v_sc = F32(W.vscale);
     const int64_t nv = z.nv, nc = z.nc;
 
-    // one forward and backward pass: loss into ws loss[0], gradient into G
-    auto pass = [&]() -> int32_t {
-        TRCHK(hipMemsetAsync(Gp, 0, 4 * PL.n, s));
-        TRCHK(hipMemsetAsync(ws + W.loss, 0, 16, s));
-        TRCHK(tr_embed_fwd(F32(W.Xv), Pp + PL.Ev, Pp + PL.ev, F32(W.Av[0]), nv, s));
-        TRCHK(tr_embed_fwd(F32(W.Xc), Pp + PL.Ec, Pp + PL.ec, F32(W.Ac[0]), nc, s));
+    float *gv = F32(W.gv), *gc = F32(W.gc), *part = F32(W.part);
+    // one forward and backward pass: loss into loss[at], gradient into G
+    // (every entry of it is a sum over partials, written once)
+    auto pass = [&](int32_t at) -> int32_t {
+        TRCHK(tr_embed_fwd(F32(W.Xv), Pp + PL.Ev, Pp + PL.ev, F32(W.Av[0]), B16(W.Bv[0]),
+                           nv, s));
+        TRCHK(tr_embed_fwd(F32(W.Xc), Pp + PL.Ec, Pp + PL.ec, F32(W.Ac[0]), B16(W.Bc[0]),
+                           nc, s));
         for (int l = 0; l < L; ++l) {
-            float *MP = F32(W.tv[0]), *MN = F32(W.tv[1]), *Uv = F32(W.tv[2]);
-            float *MQ = F32(W.tc[0]), *MR = F32(W.tc[1]), *Uc = F32(W.tc[2]);
-            TRCHK(tr_mm(F32(W.Av[l]), Pp + PL.P + l * HH, 0, MP, nv, 1.f, 0, s));
-            TRCHK(tr_mm(F32(W.Av[l]), Pp + PL.N + l * HH, 0, MN, nv, 1.f, 0, s));
-            TRCHK(tr_mm(F32(W.Ac[l]), Pp + PL.S + l * HH, 0, Uc, nc, 1.f, 0, s));
-            TRCHK(tr_segsum(c_off, c_idx, MP, MN, nullptr, c_sc, Uc, nc, 1, s));
-            TRCHK(tr_act_fwd(Uc, Pp + PL.bc + l * H, F32(W.Ac[l + 1]), nc, s));
-            TRCHK(tr_mm(F32(W.Ac[l + 1]), Pp + PL.Q + l * HH, 0, MQ, nc, 1.f, 0, s));
-            TRCHK(tr_mm(F32(W.Ac[l + 1]), Pp + PL.R + l * HH, 0, MR, nc, 1.f, 0, s));
-            TRCHK(tr_mm(F32(W.Av[l]), Pp + PL.T + l * HH, 0, Uv, nv, 1.f, 0, s));
-            TRCHK(tr_segsum(v_off, v_idx, MQ, MR, nullptr, v_sc, Uv, nv, 1, s));
-            TRCHK(tr_act_fwd(Uv, Pp + PL.bv + l * H, F32(W.Av[l + 1]), nv, s));
+            TRCHK(tr_layer_fwd(c_off, c_idx, B16(W.Bv[l]), B16(W.Bc[l]), c_sc, Pp + PL.P + l * HH,
+                               Pp + PL.N + l * HH, Pp + PL.S + l * HH, Pp + PL.bc + l * H,
+                               F32(W.Ac[l + 1]), B16(W.Bc[l + 1]), nc, s));
+            TRCHK(tr_layer_fwd(v_off, v_idx, B16(W.Bc[l + 1]), B16(W.Bv[l]), v_sc,
+                               Pp + PL.Q + l * HH, Pp + PL.R + l * HH, Pp + PL.T + l * HH,
+                               Pp + PL.bv + l * H, F32(W.Av[l + 1]), B16(W.Bv[l + 1]), nv, s));
         }
-        int cur = 0;
-        TRCHK(tr_readout(F32(W.Av[L]), F32(W.y), Pp + PL.wo, Pp + PL.bo, F32(W.dv[cur]),
-                         Gp + PL.wo, Gp + PL.bo, F32(W.loss), nv, 1.f / (float)n_lab, s));
-        TRCHK(hipMemsetAsync(ws + W.dc[cur], 0, 4 * (size_t)H * nc, s));
+        TrSegs ro;
+        ro.add(0, H, Gp + PL.wo);
+        ro.add(H, H, Gp + PL.bv + (L - 1) * H);
+        ro.add(2 * H, 1, Gp + PL.bo);
+        ro.add(2 * H + 1, 1, F32(W.loss) + at);
+        TRCHK(tr_readout(F32(W.Av[L]), F32(W.y), Pp + PL.wo, Pp + PL.bo, v_sc, gv, part, ro, nv,
+                         1.f / (float)n_lab, s));
         for (int l = L - 1; l >= 0; --l) {
-            const int nxt = 1 - cur;
-            float *dAv1 = F32(W.dv[cur]), *dAc1 = F32(W.dc[cur]);
-            float *dAv0 = F32(W.dv[nxt]), *dAc0 = F32(W.dc[nxt]);
-            float *GP = F32(W.tv[0]), *GN = F32(W.tv[1]), *gv = F32(W.tv[2]);
-            float *GQ = F32(W.tc[0]), *GR = F32(W.tc[1]), *gc = F32(W.tc[2]);
-            // variable update of layer l
-            TRCHK(tr_act_bwd(dAv1, F32(W.Av[l + 1]), gv, Gp + PL.bv + l * H, nv, s));
-            TRCHK(tr_mm_tn(F32(W.Av[l]), gv, Gp + PL.T + l * HH, nv, s));
-            TRCHK(tr_mm(gv, Pp + PL.T + l * HH, 1, dAv0, nv, 1.f, 0, s));
-            TRCHK(tr_segsum(c_off, c_idx, gv, nullptr, v_sc, nullptr, GQ, nc, 0, s));
-            TRCHK(tr_segsum(c_off, c_idx, nullptr, gv, v_sc, nullptr, GR, nc, 0, s));
-            TRCHK(tr_mm_tn(F32(W.Ac[l + 1]), GQ, Gp + PL.Q + l * HH, nc, s));
-            TRCHK(tr_mm_tn(F32(W.Ac[l + 1]), GR, Gp + PL.R + l * HH, nc, s));
-            TRCHK(tr_mm(GQ, Pp + PL.Q + l * HH, 1, dAc1, nc, 1.f, 1, s));
-            TRCHK(tr_mm(GR, Pp + PL.R + l * HH, 1, dAc1, nc, 1.f, 1, s));
-            // nogood update of layer l
-            TRCHK(tr_act_bwd(dAc1, F32(W.Ac[l + 1]), gc, Gp + PL.bc + l * H, nc, s));
-            TRCHK(tr_mm_tn(F32(W.Ac[l]), gc, Gp + PL.S + l * HH, nc, s));
-            TRCHK(tr_mm(gc, Pp + PL.S + l * HH, 1, dAc0, nc, 1.f, 0, s));
-            TRCHK(tr_segsum(v_off, v_idx, gc, nullptr, c_sc, nullptr, GP, nv, 0, s));
-            TRCHK(tr_segsum(v_off, v_idx, nullptr, gc, c_sc, nullptr, GN, nv, 0, s));
-            TRCHK(tr_mm_tn(F32(W.Av[l]), GP, Gp + PL.P + l * HH, nv, s));
-            TRCHK(tr_mm_tn(F32(W.Av[l]), GN, Gp + PL.N + l * HH, nv, s));
-            TRCHK(tr_mm(GP, Pp + PL.P + l * HH, 1, dAv0, nv, 1.f, 1, s));
-            TRCHK(tr_mm(GN, Pp + PL.N + l * HH, 1, dAv0, nv, 1.f, 1, s));
-            cur = nxt;
+            TrSegs sc;      // nogood rows of layer l
+            sc.add(0, HH, Gp + PL.Q + l * HH);
+            sc.add(HH, HH, Gp + PL.R + l * HH);
+            sc.add(2 * HH, HH, Gp + PL.S + l * HH);
+            sc.add(3 * HH, H, Gp + PL.bc + l * H);
+            const int up = l + 1 < L ? 1 : 0;
+            TRCHK(tr_layer_bwd(TR_NOGOODS, c_off, c_idx, gv, gc, up, c_sc, F32(W.Ac[l + 1]),
+                               B16(W.Bc[l + 1]), B16(W.Bc[l]), nullptr, Pp + PL.Q + l * HH, Pp + PL.R + l * HH,
+                               Pp + PL.S + (l + up) * HH, part, sc, nc, s));
+            TrSegs sv;      // variable rows: into layer l - 1's update, or the embedding
+            sv.add(0, HH, Gp + PL.P + l * HH);
+            sv.add(HH, HH, Gp + PL.N + l * HH);
+            sv.add(2 * HH, HH, Gp + PL.T + l * HH);
+            sv.add(3 * HH, H, l > 0 ? Gp + PL.bv + (l - 1) * H : Gp + PL.ev);
+            if (l == 0) sv.add(3 * HH + H, F * H, Gp + PL.Ev);
+            TRCHK(tr_layer_bwd(TR_VARS, v_off, v_idx, gc, gv, 1, v_sc, F32(W.Av[l]),
+                               B16(W.Bv[l]), nullptr, l > 0 ? nullptr : F32(W.Xv), Pp + PL.P + l * HH, Pp + PL.N + l * HH,
+                               Pp + PL.T + l * HH, part, sv, nv, s));
         }
-        // embeddings
-        float *gv = F32(W.tv[2]), *gc = F32(W.tc[2]);
-        TRCHK(tr_act_bwd(F32(W.dv[cur]), F32(W.Av[0]), gv, Gp + PL.ev, nv, s));
-        TRCHK(tr_embed_bwd(F32(W.Xv), gv, Gp + PL.Ev, nv, s));
-        TRCHK(tr_act_bwd(F32(W.dc[cur]), F32(W.Ac[0]), gc, Gp + PL.ec, nc, s));
-        TRCHK(tr_embed_bwd(F32(W.Xc), gc, Gp + PL.Ec, nc, s));
+        TrSegs se;
+        se.add(3 * HH, H, Gp + PL.ec);
+        se.add(3 * HH + H, F * H, Gp + PL.Ec);
+        TRCHK(tr_layer_bwd(TR_EMBED_NOGOODS, nullptr, nullptr, nullptr, gc, 1, c_sc, F32(W.Ac[0]),
+                           nullptr, nullptr, F32(W.Xc), nullptr, nullptr, Pp + PL.S, part, se, nc, s));
         return ASP_OK;
     };
 
     if (steps == 0) {
-        int32_t rc = pass();
+        int32_t rc = pass(0);
         if (rc) return rc;
         float loss = 0.f;
         TRCHK(hipMemcpyAsync(&loss, ws + W.loss, 4, hipMemcpyDeviceToHost, s));
@@ -409,12 +402,12 @@ int32_t train_run(const std::vector<const HostProgram*>& progs, const float* lab
         return ASP_OK;
     }
     for (int32_t t = 1; t <= steps; ++t) {
-        int32_t rc = pass();
+        int32_t rc = pass(t - 1);
         if (rc) return rc;
-        if (loss_out)
-            TRCHK(hipMemcpyAsync(loss_out + (t - 1), ws + W.loss, 4, hipMemcpyDeviceToHost, s));
         TRCHK(tr_adam(Pp, Gp, F32(W.M), F32(W.V), PL.n, lr, t, ws + W.range, F32(W.lim), s));
     }
+    if (loss_out)
+        TRCHK(hipMemcpyAsync(loss_out, ws + W.loss, 4 * (size_t)steps, hipMemcpyDeviceToHost, s));
     TRCHK(hipMemcpyAsync(params, Pp, 4 * PL.n, hipMemcpyDeviceToHost, s));
     if (grad_out) TRCHK(hipMemcpyAsync(grad_out, Gp, 4 * PL.n, hipMemcpyDeviceToHost, s));
     TRCHK(hipStreamSynchronize(s));

@@ -131,3 +131,94 @@ def test_batch_learned_nogoods_are_the_oracles(P):
         o_lits = st.ng_lits[base:].astype(np.int32)
         off, lits = b.learned(i)
         assert np.array_equal(off, o_off) and np.array_equal(lits, o_lits), i
+
+
+@pytest.mark.parametrize("atoms,rules,copies", [(4, 4, 1), (16, 16, 2), (13, 17, 2), (16, 16, 4),
+                                                (60, 200, 8), (700, 2100, 4)])
+def test_gradient_over_row_tiles(P, atoms, rules, copies):
+    """The mean loss of a program's copies, and its gradient, are the
+    program's own: the copies' rows fall at other places of the 64-row tiles
+    (64 variable rows exactly, one more, one less, many tiles).  A copy count
+    that is a power of two scales every term exactly, so what differs is the
+    order of the float32 sums over rows: for n rows, about sqrt(n) 2^-24 of
+    the terms' size, below 1e-4 here even after some cancellation.  Two runs
+    give the same bits."""
+    from paper_1909_01786_amd import binding as B
+    rng = np.random.default_rng(atoms)
+    prog = aspgen.random_program(np.random.default_rng(rules), atoms, rules, 0, 3)
+    lab = rng.integers(0, 2, atoms).astype(np.float32)
+    w = aspgen.mpnn_weights(atoms, spread=40)
+    for k in ("ev", "ec", "bc", "bv"):
+        w[k] = w[k] // 8
+    vec = B.dequantize(w)
+    gp = [P.Program(prog) for _ in range(copies)]
+    _, l1, g1 = B.train_scorer(gp[:1], [lab], vec, steps=0)
+    _, ln, gn = B.train_scorer(gp, [lab] * copies, vec, steps=0)
+    _, lm, gm = B.train_scorer(gp, [lab] * copies, vec, steps=0)
+    assert np.array_equal(gn, gm) and np.array_equal(ln, lm)
+    assert abs(l1[0] - ln[0]) <= 1e-5 * abs(l1[0])
+    a, b = T.split(gn.astype(np.float64)), T.split(g1.astype(np.float64))
+    for name, _ in T.layout():
+        d, n = np.linalg.norm(a[name] - b[name]), np.linalg.norm(b[name])
+        assert d <= 1e-4 * n + 1e-9, (name, d, n)
+    # against float64 arithmetic with the same bfloat16 operands; float32
+    # sums move a product by about 2^-20 and now and then an operand across
+    # a rounding boundary (2^-9 of it), a few 1e-5 of each term
+    rl, rg = _rounded_gradient(vec, prog, lab)
+    assert abs(l1[0] - rl) <= 1e-4 * abs(rl)
+    assert np.linalg.norm(g1 - rg) <= 1e-2 * np.linalg.norm(rg)
+
+
+def _rounded_gradient(vec, prog, lab):
+    """Loss and gradient in float64 with the operands of every 64-wide
+    product -- activations, matrices, backward derivatives -- rounded to
+    bfloat16, the derivatives written out by hand."""
+    W = {k: v for k, v in T.split(torch.tensor(vec.astype(np.float64))).items()}
+    g, xv, xc, deg = T.graph_tensors(prog)
+    xv, xc = torch.tensor(xv), torch.tensor(xc)
+    v, c, pos = torch.tensor(g.var - 1), torch.tensor(g.ng_of_lit), torch.tensor(g.pos)
+    cs = torch.tensor(2.0 ** -T.log2ceil(g.lens).astype(np.float64))[:, None]
+    vs = torch.tensor(2.0 ** -T.log2ceil(deg).astype(np.float64))[:, None]
+
+    def R(x):
+        return x.to(torch.float32).to(torch.bfloat16).to(torch.float64)
+
+    def edges(n, dst, src, x, m):
+        return torch.zeros((n, 64), dtype=torch.float64).index_add(0, dst[m], x[src[m]])
+
+    def mask(d, a):
+        return torch.where((a > 0) & (a < 1), d, torch.zeros_like(d))
+    L = 3
+    av, ac = [torch.clamp(xv @ W["Ev"] / 4 + W["ev"], 0, 1)], [torch.clamp(xc @ W["Ec"] / 4 + W["ec"], 0, 1)]
+    for l in range(L):
+        e = edges(g.n, c, v, R(av[l]) @ R(W["P"][l]), pos) + edges(g.n, c, v, R(av[l]) @ R(W["N"][l]), ~pos)
+        ac.append(torch.clamp((R(ac[l]) @ R(W["S"][l]) + cs * e) / 4 + W["bc"][l], 0, 1))
+        e = edges(g.V, v, c, R(ac[l + 1]) @ R(W["Q"][l]), pos) + \
+            edges(g.V, v, c, R(ac[l + 1]) @ R(W["R"][l]), ~pos)
+        av.append(torch.clamp((R(av[l]) @ R(W["T"][l]) + vs * e) / 4 + W["bv"][l], 0, 1))
+    y = torch.tensor(lab.astype(np.float64))
+    A = y.shape[0]
+    z = av[L][:A] @ W["wo"] + W["bo"]
+    loss = torch.nn.functional.binary_cross_entropy_with_logits(z, y)
+    dz = (torch.sigmoid(z) - y) / A
+    G = {k: torch.zeros_like(x) for k, x in W.items()}
+    G["wo"], G["bo"] = dz @ av[L][:A], dz.sum()
+    dv, dc = torch.zeros_like(av[L]), torch.zeros_like(ac[L])
+    dv[:A] = dz[:, None] * W["wo"]
+    for l in reversed(range(L)):
+        m = mask(dv, av[l + 1])
+        G["bv"][l], gv = m.sum(0), m / 4
+        gq, gr = edges(g.n, c, v, vs * gv, pos), edges(g.n, c, v, vs * gv, ~pos)
+        G["T"][l] = R(av[l]).T @ R(gv)
+        G["Q"][l], G["R"][l] = R(ac[l + 1]).T @ R(gq), R(ac[l + 1]).T @ R(gr)
+        m = mask(dc + R(gq) @ R(W["Q"][l]).T + R(gr) @ R(W["R"][l]).T, ac[l + 1])
+        G["bc"][l], gc = m.sum(0), m / 4
+        gp, gn = edges(g.V, v, c, cs * gc, pos), edges(g.V, v, c, cs * gc, ~pos)
+        G["S"][l] = R(ac[l]).T @ R(gc)
+        G["P"][l], G["N"][l] = R(av[l]).T @ R(gp), R(av[l]).T @ R(gn)
+        dv = R(gv) @ R(W["T"][l]).T + R(gp) @ R(W["P"][l]).T + R(gn) @ R(W["N"][l]).T
+        dc = R(gc) @ R(W["S"][l]).T
+    for name, x, d, a in (("v", xv, dv, av[0]), ("c", xc, dc, ac[0])):
+        m = mask(d, a)
+        G["e" + name], G["E" + name] = m.sum(0), x.T @ (m / 4)
+    return float(loss), np.concatenate([G[k].numpy().reshape(-1) for k, _ in T.layout()])
