@@ -98,7 +98,7 @@ struct Plan {
     std::vector<int64_t> slot_off;      // per instance, bytes from off_slots
     uint64_t off_desc = 0, off_order = 0, off_slotoff = 0, off_ngo = 0, off_ngl = 0, off_mo = 0,
              off_mi = 0, off_rh = 0, off_ro = 0, off_rbo = 0, off_rbl = 0, off_asc = 0,
-             off_rs = 0, off_rord = 0, off_rords = 0, off_rsort = 0, off_verd = 0, off_stats = 0, off_models = 0, off_slots = 0, total = 0;
+             off_rord = 0, off_rords = 0, off_rsort = 0, off_verd = 0, off_stats = 0, off_models = 0, off_slots = 0, total = 0;
     int64_t tot_ngo = 0, tot_ngl = 0, tot_mo = 0, tot_mi = 0, tot_rules = 0, tot_rbo = 0,
             tot_rbl = 0, tot_model = 0, tot_asc = 0, slots_bytes = 0;
     size_t max_lds() const {
@@ -308,7 +308,6 @@ int32_t make_plan(const std::vector<const HostProgram*>& progs, const asp_option
     P.off_rbo = take(4 * (uint64_t)P.tot_rbo);
     P.off_rbl = take(4 * (uint64_t)P.tot_rbl);
     P.off_asc = take(4 * (uint64_t)P.tot_asc);
-    P.off_rs = take(4 * (uint64_t)P.tot_rules);
     P.off_rord = take(8 * (uint64_t)P.tot_rules);
     P.off_rords = take(8 * (uint64_t)P.tot_rules);
     P.off_rsort = take(8 * (uint64_t)P.tot_rules);
@@ -381,7 +380,6 @@ KArgs make_args(const Plan& P, uint8_t* arena, int32_t mode, const LaunchClass& 
     a.map_ent = (const MapEntry*)(arena + P.off_mi);
     a.rule_head = (const int32_t*)(arena + P.off_rh);
     a.rule_occ = (const int32_t*)(arena + P.off_ro);
-    a.rule_score = (const int32_t*)(arena + P.off_rs);
     a.rule_ord = (const int32_t*)(arena + P.off_rord);
     a.rule_ord_sc = (const int32_t*)(arena + P.off_rords);
     a.rb_off = (const int32_t*)(arena + P.off_rbo);
@@ -534,7 +532,6 @@ int32_t put_scores(const Plan& P, uint8_t* arena, int32_t i, const int32_t* scor
     a.inst = (const InstDesc*)(arena + P.off_desc);
     a.rule_head = (const int32_t*)(arena + P.off_rh);
     a.atom_score = (int32_t*)(arena + P.off_asc);
-    a.rule_score = (int32_t*)(arena + P.off_rs);
     a.rule_ord_sc = (int32_t*)(arena + P.off_rords);
     a.sort_tmp = (unsigned long long*)(arena + P.off_rsort);
     a.inst_list = nullptr;   // gather instance i only
@@ -685,7 +682,6 @@ ScorerArgs scorer_args(const std::vector<const HostProgram*>& progs, const Plan&
     a.n_inst = (int32_t)progs.size();
     a.ws = ws;
     a.atom_score = (int32_t*)(arena + P.off_asc);
-    a.rule_score = (int32_t*)(arena + P.off_rs);
     a.rule_ord_sc = (int32_t*)(arena + P.off_rords);
     a.sort_tmp = (unsigned long long*)(arena + P.off_rsort);
     return a;

@@ -4,8 +4,8 @@
 //   [static]  per-instance descriptors, the instance order, and every
 //             instance's completion nogoods (CSR), literal->nogood map (CSR),
 //             rule table and rule bodies, packed one instance after another;
-//   [scores]  per-instance decision scores of atoms and of rules (the score
-//             of each rule's head), written before a score-driven search;
+//   [scores]  per-instance decision scores of atoms, and the rules in their
+//             heads' score order, written before a score-driven search;
 //   [results] verdicts, per-instance counters, model bytes;
 //   [slots]   one dynamic search state per instance, sized for it.
 //
@@ -178,7 +178,6 @@ struct KArgs {
     const MapEntry* map_ent;
     const int32_t* rule_head;
     const int32_t* rule_occ;
-    const int32_t* rule_score;   // score of each rule's head (score-driven Decision)
     const int32_t* rule_ord;     // (rule, head) pairs in the static score's Decision order
     const int32_t* rule_ord_sc;  // (rule, head) pairs in the supplied scores' Decision order
     const int32_t* rb_off;

@@ -26,7 +26,6 @@ struct ScorerArgs {
     int32_t single;              // or, with inst_list null, this one instance
     uint8_t* ws;
     int32_t* atom_score;
-    int32_t* rule_score;
     int32_t* rule_ord_sc;              // (rule, head) pairs by rule score, descending
     unsigned long long* sort_tmp;      // one 8-byte word per rule (sort buffer)
 };

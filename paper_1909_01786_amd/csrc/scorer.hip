@@ -416,9 +416,8 @@ DEV unsigned long long score_key(int score, int j) {
 
 constexpr int kSortChunk = 1024;
 
-// rule_score[r] = atom_score[head(r)] for every headed rule of the listed
-// instances, and rule_ord_sc = the (rule, head) pairs in the Decision's
-// order under these scores: chunks of kSortChunk keys sorted in LDS by a
+// rule_ord_sc = the (rule, head) pairs of the listed instances' headed rules in
+// the Decision's order under their heads' atom scores: chunks of kSortChunk keys sorted in LDS by a
 // bitonic network, then merged pairwise in global memory (each key's place
 // in the merged run is its index in its own run plus the number of keys
 // below it in the other run, found by binary search; keys are distinct),
@@ -434,7 +433,6 @@ __global__ __launch_bounds__(NT) void k_rule_scores(ScorerArgs a) {
         unsigned long long* B = a.sort_tmp + d.rules;
         for (int j = tid; j < Rh; j += NT) {
             const int sc = a.atom_score[d.ascore + a.rule_head[d.rules + j]];
-            a.rule_score[d.rules + j] = sc;
             A[j] = score_key(sc, j);
         }
         __syncthreads();

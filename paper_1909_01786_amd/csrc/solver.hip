@@ -124,7 +124,7 @@ struct LdsMap {
 
 struct Ctx {
     // per-instance static arrays
-    const int32_t *NO, *NL, *MO, *RH, *RO, *RS, *RD, *RDS, *RBO, *RBL;
+    const int32_t *NO, *NL, *MO, *RH, *RO, *RD, *RDS, *RBO, *RBL;
     const MapEntry* ME;
     // per-slot arrays
     SlotCtrl* ctrl;
@@ -427,7 +427,6 @@ DEV void bind_instance(Ctx& c, Ctl& k, const KArgs& a, int inst) {
     c.ME = a.map_ent + d.map_ids;
     c.RH = a.rule_head + d.rules;
     c.RO = a.rule_occ + d.rules;
-    c.RS = a.rule_score + d.rules;
     c.RD = a.rule_ord + 2 * d.rules;
     c.RDS = a.rule_ord_sc + 2 * d.rules;
     c.RBO = a.rb_off + d.rb_off;
@@ -2095,34 +2094,34 @@ DEV void at_fixpoint(Ctl& k) {
     if (k.dec_open) k.consec = 0;
 }
 
-// This lane's best applicable rule: key (score of the head, biased to keep
-// its order as unsigned) << 32 | (~rule), 0 if none.  BY_ACT reads the
-// head's activity, else score[j]; four rules per lane at a time, so their
-// loads are issued together.
-template <bool BY_ACT, bool BELOW = false>
-DEV unsigned long long best_rule(Ctx& c, const Ctl& k, const int32_t* score,
-                                 unsigned long long below = 0ull) {
+// This lane's best applicable rule under the activity: key (activity of the
+// head, biased to keep its order as unsigned) << 32 | (~rule), 0 if none;
+// BELOW: among the keys below `below`.  The LDS tests come first, so that
+// only an applicable rule's activity is read; four rules per lane at a time,
+// so their loads are issued together.
+template <bool BELOW>
+DEV unsigned long long best_rule(Ctx& c, const Ctl& k, unsigned long long below = 0ull) {
     const int T = c.T, A = k.A, Rh = k.Rh;
     unsigned long long best = 0ull;
     constexpr int U = 4;
     for (int j0 = c.tid; j0 < Rh; j0 += U * T) {
         int hp[U], sc[U];
+        bool cand[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int j = j0 + u * T;
-            hp[u] = j < Rh ? c.RH[j] : 0;
-            if (!BY_ACT) sc[u] = j < Rh ? score[j] : 0;
-        }
-        if (BY_ACT) {
-#pragma unroll
-            for (int u = 0; u < U; ++u) sc[u] = j0 + u * T < Rh ? c.act[hp[u]] : 0;
+            const int j = j0 + u * T, t = A + 3 * j + 2;
+            cand[u] = j < Rh && vget(c.valb, t) == VT && vget(c.valb, t + 1) != VF;
+            hp[u] = cand[u] ? c.RH[j] : 0;
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
+            cand[u] = cand[u] && vget(c.valb, hp[u]) == 0u;
+            sc[u] = cand[u] ? c.act[hp[u]] : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
             const int j = j0 + u * T;
-            if (j >= Rh || vget(c.valb, hp[u]) != 0u) continue;
-            const int t = A + 3 * j + 2;
-            if (vget(c.valb, t) != VT || vget(c.valb, t + 1) == VF) continue;
+            if (!cand[u]) continue;
             const unsigned long long key =
                 ((unsigned long long)((uint32_t)sc[u] ^ 0x80000000u) << 32) |
                 (unsigned long long)(0xffffffffu - (uint32_t)j);
@@ -2137,16 +2136,17 @@ DEV unsigned long long best_rule(Ctx& c, const Ctl& k, const int32_t* score,
 // (the static table, or supplied scores): the first candidate in the
 // order `ord` of the rules (score descending, then rule ascending; sorted
 // by the host for the static table, on the device for supplied scores) is
-// the candidate of greatest (score, -rule) key, the one best_rule finds.  Each
+// the candidate of greatest (score, -rule) key, the one a scan would find.  Each
 // wave scans its own 64-position chunks of that order (wave w: chunks w,
 // w + nw, ...), four in flight, and stops at its first chunk that holds a
-// candidate; the block keeps the lowest position.  Returns
+// candidate; the block keeps the lowest position.  `from`: the positions
+// before it are left out (the next candidates, for the lookahead).  Returns
 // (2^32-1 - position) << 32 | rule for the caller's block maximum, 0 when no
 // rule is a candidate.
-DEV unsigned long long first_rule(Ctx& c, const Ctl& k, const int32_t* ord) {
+DEV unsigned long long first_rule(Ctx& c, const Ctl& k, const int32_t* ord, int from = 0) {
     const int Rh = k.Rh, A = k.A, nw = c.nw, lane = c.lane;
     constexpr int U = 4;
-    for (int p0 = c.wid * 64; p0 < Rh; p0 += U * nw * 64) {
+    for (int p0 = (from & ~63) + c.wid * 64; p0 < Rh; p0 += U * nw * 64) {
         int jj[U], hh[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -2158,7 +2158,7 @@ DEV unsigned long long first_rule(Ctx& c, const Ctl& k, const int32_t* ord) {
         for (int u = 0; u < U; ++u) {
             const int p = p0 + u * nw * 64 + lane;
             bool cand = false;
-            if (p < Rh && vget(c.valb, hh[u]) == 0u) {
+            if (p < Rh && p >= from && vget(c.valb, hh[u]) == 0u) {
                 const int t = A + 3 * jj[u] + 2;
                 cand = vget(c.valb, t) == VT && vget(c.valb, t + 1) != VF;
             }
@@ -2212,26 +2212,26 @@ DEV int rule_of(unsigned long long key) { return (int)(0xffffffffu - (uint32_t)(
 // the values cleared (Deps of unassigned variables are never read).  With
 // no trial standing, the candidate with the most assignments (earliest on
 // ties) is decided.
-DEV void lookahead_decide(Ctx& c, Ctl& k, unsigned long long best, const int32_t* score) {
+DEV void lookahead_decide(Ctx& c, Ctl& k, unsigned long long best, const int32_t* ord) {
     const int T = c.T, tid = c.tid;
-    unsigned long long keys[8];
-    int n = 1;
-    keys[0] = best;
+    int rules[8];
+    int n = 0;
     const bool by_act = c.decision == DECISION_ACTIVITY;
-    for (int i = 1; i < c.lookahead && i < 8; ++i) {
-        const unsigned long long mine = by_act ? best_rule<true, true>(c, k, c.RO, keys[i - 1])
-                                               : best_rule<false, true>(c, k, score, keys[i - 1]);
-        const unsigned long long nxt = block_max_u64(c, mine);
+    while (best != 0ull) {
+        rules[n++] = by_act ? rule_of(best) : (int)(uint32_t)best;
+        if (n >= c.lookahead || n >= 8) break;
+        const unsigned long long mine =
+            by_act ? best_rule<true>(c, k, best)
+                   : first_rule(c, k, ord, (int)(0xffffffffu - (uint32_t)(best >> 32)) + 1);
+        best = block_max_u64(c, mine);
         bar();
-        if (nxt == 0ull) break;
-        keys[n++] = nxt;
     }
-    int pick = rule_of(best);
+    int pick = rules[0];
     if (n > 1) {
         const int consec0 = k.consec, open0 = k.dec_open, cdl0 = k.cdl, qt0 = k.qt;
         int best_p = -1;
         for (int i = 0; i < n; ++i) {
-            const int j = rule_of(keys[i]);
+            const int j = rules[i];
             decide_rule(c, k, j);
             k.dec_open = 1;
             while (k.qt > k.qh && !k.pend_kind && k.status == ST_RUNNING) {
@@ -2271,26 +2271,20 @@ DEV void lookahead_decide(Ctx& c, Ctl& k, unsigned long long best, const int32_t
 DEV int step_decide_or_complete(Ctx& c, Ctl& k) {
     const int T = c.T, tid = c.tid, W = c.W, A = k.A;
     at_fixpoint(k);
-    // key: head score (signed, biased to keep its order) then lowest rule;
-    // the score is the static per-rule table (occurrences or Jeroslow-Wang),
-    // the supplied scores, or the head's activity
-    const int32_t* score = k.use_score ? c.RS : c.RO;
-    unsigned long long best;
-    int j;
-    if (!c.ext) {
-        best = block_max_u64(c, first_rule(c, k, k.use_score ? c.RDS : c.RD));
-        j = (int)(uint32_t)(best & 0xffffffffull);
-    } else {
-        const unsigned long long mine = c.ext && c.decision == DECISION_ACTIVITY
-                                            ? best_rule<true>(c, k, c.RO)
-                                            : best_rule<false>(c, k, score);
-        best = block_max_u64(c, mine);
-        j = rule_of(best);
-    }
+    // the candidate of greatest (score of the head, -rule): under the static
+    // table (occurrences or Jeroslow-Wang) or supplied scores the first one
+    // in their order (full scans for each candidate took 10 us a Decision on
+    // the enumerated batches, and 40 of the lookahead's 196), under the
+    // activity, which changes during the search, by a scan
+    const bool by_act = c.ext && c.decision == DECISION_ACTIVITY;
+    const int32_t* ord = k.use_score ? c.RDS : c.RD;
+    const unsigned long long best =
+        block_max_u64(c, by_act ? best_rule<false>(c, k) : first_rule(c, k, ord));
+    const int j = by_act ? rule_of(best) : (int)(uint32_t)best;
     bar();
     if (best != 0ull) {
         if (c.ext && c.lookahead > 1) {
-            lookahead_decide(c, k, best, score);
+            lookahead_decide(c, k, best, ord);
             return STEP_DECIDE;
         }
         decide_rule(c, k, j);

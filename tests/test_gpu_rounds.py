@@ -72,3 +72,19 @@ def test_learned_visits(P, seed, learning):
     for prog in (aspgen.single_random(1000 + seed), aspgen.batch_hamiltonian(seed, n_lo=20, n_hi=30)):
         for n in (50, 200, 400):
             _compare(P, prog, n, 128, learning=learning)
+
+
+@pytest.mark.parametrize("threads", [64, 128, 256])
+@pytest.mark.parametrize("decision", [0, 2, 3])
+@pytest.mark.parametrize("lookahead", [2, 8])
+def test_ordered_candidates(P, lookahead, decision, threads):
+    """The lookahead's candidates, taken one after another from the rules'
+    order: neighbours in one 64-position chunk (a colouring's first
+    decisions), spread over many chunks, and fewer than asked for."""
+    for prog in (aspgen.gnp_coloring(1, 40, 3.0), fan(5, 2), aspgen.batch_random(3, a_lo=200, a_hi=400)):
+        g = P.Program(prog, lookahead=lookahead, decision=decision).bind("cuda", threads=threads)
+        rc, m, st = g.solve(P.limits(60, 30000))
+        orc, om, ost = oracle.solve(prog, lookahead=lookahead, decision=decision,
+                                    limits=oracle.make_limits(60))
+        assert rc == STATUS[orc], prog.name
+        assert_same_stats(ost, st, prog.name)
