@@ -110,7 +110,8 @@ WsLayout ws_layout(const Sizes& z) {
     W.range = take(PL.n);
     W.lim = take(4 * 4);
     W.loss = take(4 * (uint64_t)kMaxSteps);
-    W.part = take(4 * (uint64_t)kTrParts * kTrPart);
+    W.part = take(4 * std::max<uint64_t>((uint64_t)kTrParts * kTrPart,
+                                         (uint64_t)tr_readout_waves(z.nv) * (2 * H + 2)));
     W.Xv = take(4 * F * z.nv);
     W.Xc = take(4 * F * z.nc);
     W.coff = take(8 * (z.nc + 1));

@@ -39,6 +39,8 @@ hipError_t tr_layer_bwd(int kind, const int64_t* off, const int32_t* idx, const 
                         int has_own, const float* scale, const float* X1, const uint16_t* B1,
                         const uint16_t* B0, const float* X8, const float* Wa, const float* Wb,
                         const float* Wc, float* part, const TrSegs& sg, int64_t rows, hipStream_t s);
+// Partials (2 * 64 + 2 floats each) that the readout's `part` takes.
+int64_t tr_readout_waves(int64_t rows);
 hipError_t tr_readout(const float* A, const float* y, const float* wo, const float* bo,
                       const float* scale, float* G, float* part, const TrSegs& sg, int64_t rows,
                       float inv_n, hipStream_t s);

@@ -472,7 +472,9 @@ __global__ __launch_bounds__(NT) void k_sum_parts(const float* part, int64_t str
 // adds softplus(z) - y z (binary cross-entropy with logits) / n_lab; the
 // derivative by the row's activations, (sigmoid(z) - y) / n_lab wo, is
 // masked and scaled as the backward kernels' results are.  One wave per
-// row.  part: [64] by wo, [64] by the last bias, by bo, the loss.
+// row, about sixteen rows a wave.  part, a wave each: [64] by wo, [64] by the
+// last bias, by bo, the loss.
+constexpr int kReadout = 2 * H + 2;
 __global__ __launch_bounds__(NT) void k_readout(const float* A, const float* y, const float* wo,
                                                 const float* bo, const float* scale, float* G,
                                                 float* part, int64_t rows, float inv_n) {
@@ -502,16 +504,69 @@ __global__ __launch_bounds__(NT) void k_readout(const float* A, const float* y, 
             ls += (fmaxf(z, 0.f) - z * lab + log1pf(__expf(-fabsf(z)))) * inv_n;
         }
     }
-    __shared__ float red[4][2 * H + 2];
-    red[wv][lane] = gw;
-    red[wv][H + lane] = db;
+    float* o = part + ((size_t)blockIdx.x * (NT / 64) + wv) * kReadout;
+    o[lane] = gw;
+    o[H + lane] = db;
     if (lane == 0) {
-        red[wv][2 * H] = gb;
-        red[wv][2 * H + 1] = ls;
+        o[2 * H] = gb;
+        o[2 * H + 1] = ls;
     }
+}
+
+// The readout's sums: each column one float32 running sum over the waves'
+// partials, in their order.  What a long running sum rounds away, all the same
+// way, is up to 3e-5 of the loss and of the last bias's gradient at 0.8M rows:
+// a sum over a tree leaves it out and moves both by that much, so the order is
+// part of the result.  One workgroup: a thread per column adds a chunk in LDS
+// while all threads load the next.  The chain of additions bounds it (48
+// thousand partials on 64 programs; their loads alone would take 5 us).
+constexpr int kRunRows = 128, kRunT = 1024;
+__global__ __launch_bounds__(kRunT) void k_running_sums(const float* part, int64_t n, TrSegs sg) {
+    __shared__ __attribute__((aligned(16))) float buf[2][kRunRows * kReadout];
+    constexpr int N4 = kRunRows * kReadout / 4, PER = (N4 + kRunT - 1) / kRunT;
+    const int tid = threadIdx.x;
+    const int64_t all = n * kReadout;
+    float4 x[PER];
+    auto load = [&](int64_t row) {
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const int i = tid + k * kRunT;
+            const int64_t at = row * kReadout + 4 * (int64_t)i;
+            x[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (i >= N4) continue;
+            if (at + 4 <= all) {
+                x[k] = *(const float4*)(part + at);
+            } else {
+                if (at < all) x[k].x = part[at];
+                if (at + 1 < all) x[k].y = part[at + 1];
+                if (at + 2 < all) x[k].z = part[at + 2];
+            }
+        }
+    };
+    auto keep = [&](float* b) {
+#pragma unroll
+        for (int k = 0; k < PER; ++k)
+            if (tid + k * kRunT < N4) ((float4*)b)[tid + k * kRunT] = x[k];
+    };
+    float s = 0.f;
+    load(0);
+    keep(buf[0]);
     __syncthreads();
-    for (int i = threadIdx.x; i < 2 * H + 2; i += NT)
-        part[(size_t)blockIdx.x * (2 * H + 2) + i] = (red[0][i] + red[1][i]) + (red[2][i] + red[3][i]);
+    int cur = 0;
+    for (int64_t r = 0; r < n; r += kRunRows) {
+        load(r + kRunRows);
+        if (tid < kReadout) {
+            const float* b = buf[cur] + tid;
+#pragma unroll 32
+            for (int i = 0; i < kRunRows; ++i) s += b[i * kReadout];
+        }
+        keep(buf[cur ^ 1]);
+        __syncthreads();
+        cur ^= 1;
+    }
+    if (tid >= kReadout) return;
+    for (int k = 0; k < sg.n; ++k)
+        if (tid >= sg.src[k] && tid < sg.src[k] + sg.len[k]) sg.dst[k][tid - sg.src[k]] = s;
 }
 
 // Adam (beta1 0.9, beta2 0.999, eps 1e-8) on n parameters at step t (1-based);
@@ -593,15 +648,20 @@ hipError_t tr_layer_bwd(int kind, const int64_t* off, const int32_t* idx, const 
     return sum_parts(part, kTrPart, grid * kBwdTeams, sg, s);
 }
 
+int64_t tr_readout_waves(int64_t rows) {
+    return (int64_t)grid_for(rows, (NT / 64) * 16) * (NT / 64);
+}
+
 hipError_t tr_readout(const float* A, const float* y, const float* wo, const float* bo,
                       const float* scale, float* G, float* part, const TrSegs& sg, int64_t rows,
                       float inv_n, hipStream_t s) {
     if (rows <= 0) return hipSuccess;
-    const int g = grid_for(rows, NT / 64), grid = g < 1024 ? g : 1024;
+    const int grid = tr_readout_waves(rows) / (NT / 64);
     hipLaunchKernelGGL(k_readout, dim3(grid), dim3(NT), 0, s, A, y, wo, bo, scale, G, part, rows, inv_n);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return sum_parts(part, 2 * H + 2, grid, sg, s);
+    hipLaunchKernelGGL(k_running_sums, dim3(1), dim3(kRunT), 0, s, part, (int64_t)grid * (NT / 64), sg);
+    return hipGetLastError();
 }
 
 hipError_t tr_adam(float* p, const float* g, float* m, float* v, int64_t n, float lr, int t,
