@@ -24,7 +24,7 @@
 #include "train.h"
 
 namespace asp {
-size_t lds_bytes(int threads, int words, int awords, int owords, int learning);
+size_t lds_bytes(int threads, int fc, int words, int awords, int owords, int learning);
 hipError_t launch_search(const KArgs& a, int threads, int grid, size_t lds, hipStream_t s);
 hipError_t set_max_lds(int threads, size_t lds);
 }  // namespace asp
@@ -82,7 +82,7 @@ bool valid_threads(int t) { return t == 64 || t == 128 || t == 256 || t == 512 |
 // One launch of the search kernel: instances order[first .. first+count),
 // LDS sized for the largest of them.
 struct LaunchClass {
-    int32_t first = 0, count = 0, words = 1, awords = 1, owords = 0, threads = 128;
+    int32_t first = 0, count = 0, words = 1, awords = 1, owords = 0, threads = 128, fc = 128;
     size_t lds = 0;
 };
 
@@ -182,6 +182,17 @@ asp_options default_options() {
 
 // LDS a workgroup can hold on gfx950 (static part included).
 constexpr size_t kLdsPerGroup = 160 * 1024 - 1024;
+
+// Frontier records and implication slots a workgroup keeps in LDS (and half
+// its winner table).  A round that implies more variables finds the rest's
+// Deps, map segments and learned lists in memory again, five dependent
+// gathers for each thread's share, and the next one cannot start from LDS.
+// The larger programs' rounds in the middle of a cascade imply hundreds; with
+// 128 records (one per thread) a pass of 1024 random programs of 100..5000
+// atoms took 370 ms, so 315; a 2000-vertex colouring 49 and 45.5 ms (256
+// records, and 512).  Below 4096 variables 256 do, and leave the LDS to eight
+// workgroups a CU.
+int32_t front_records(int64_t V) { return V <= 4095 ? 256 : V <= 32767 ? 512 : 1024; }
 
 // LDS size classes by variable count (the 2-bit maps take V/4 bytes each).
 std::vector<int64_t> class_bounds(int32_t classes) {
@@ -283,10 +294,13 @@ int32_t make_plan(const std::vector<const HostProgram*>& progs, const asp_option
         // the learned-occurrence bits (Fwd-learning) only where they fit: a
         // program that fits the LDS without them is not refused for them
         lc.owords = P.learning == ASP_LEARN_FWD ? (int32_t)((omax + 1 + 31) / 32) : 0;
-        lc.lds = lds_bytes(lc.threads, lc.words, lc.awords, lc.owords, P.learning);
+        const int32_t least = std::max(lc.threads, 128);
+        lc.fc = std::max(least, front_records(vmax));
+        auto fit = [&] { lc.lds = lds_bytes(lc.threads, lc.fc, lc.words, lc.awords, lc.owords, P.learning); };
+        for (fit(); lc.lds > kLdsPerGroup && lc.fc > least; fit()) lc.fc /= 2;
         if (lc.lds > kLdsPerGroup) {
             lc.owords = 0;
-            lc.lds = lds_bytes(lc.threads, lc.words, lc.awords, 0, P.learning);
+            fit();
         }
         P.classes.push_back(lc);
     }
@@ -402,6 +416,7 @@ KArgs make_args(const Plan& P, uint8_t* arena, int32_t mode, const LaunchClass& 
     a.words = lc.words;
     a.awords = lc.awords;
     a.owords = lc.owords;
+    a.fc = lc.fc;
     a.step_mask = 0;
     a.max_steps = -1;
     a.max_conflicts = -1;

@@ -204,7 +204,7 @@ struct KArgs {
     int32_t lookahead;           // Decision candidates tried by propagation (<= 1: off)
     int32_t awords;              // LDS words of the 1-bit atom map (this launch's largest A)
     int32_t owords;              // LDS words of the learned-occurrence bits, 0 without them
-    int32_t pad1;
+    int32_t fc;                  // LDS frontier records (128, 256, 512 or 1024; at least one per thread)
 };
 
 }  // namespace asp

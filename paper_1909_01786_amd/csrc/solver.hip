@@ -50,10 +50,11 @@ constexpr uint32_t NO_ENTRY = 0xffffffffu;      // implier without a map entry (
 constexpr uint64_t FNV_BASIS = 1469598103934665603ull;
 constexpr uint64_t FNV_PRIME = 1099511628211ull;
 constexpr int kMaxWaves = 16;
-constexpr int kFrontCap = 128;   // frontier records, and implication slots (Deps candidate and
-                                 // record), in LDS (at least; one per thread for wider workgroups)
-constexpr int kWinBits = 8;
-constexpr int kWinCap = 1 << kWinBits;   // LDS winner table (variables implied in a round)
+// Entries of the LDS winner table (variables implied in a round) for FC
+// frontier records and implication slots.
+__host__ __device__ constexpr int win_bits(int fc) {
+    return fc <= 128 ? 8 : fc <= 256 ? 9 : fc <= 512 ? 10 : 11;
+}
 constexpr int kWinProbe = 32;
 constexpr uint32_t SLOT_TAG = 0x80000000u;
 constexpr int kLitBatch = 4;     // literals of a long nogood loaded together in a visit
@@ -103,13 +104,14 @@ struct Scr {
 // frontier records and implication slots.  The per-instance maps follow.
 template <int FC>
 struct LdsMap {
+    static constexpr int wbits = win_bits(FC), wcap = 1 << wbits;
     static constexpr uint32_t sB = 0;
     static constexpr uint32_t tWin = sB + 8 * kMaxW;
-    static constexpr uint32_t iDeps = tWin + 8 * kWinCap;
+    static constexpr uint32_t iDeps = tWin + 8 * wcap;
     static constexpr uint32_t fDeps = iDeps + 8 * FC;
     static constexpr uint32_t tKey = fDeps + 8 * FC;
-    static constexpr uint32_t tCode = tKey + 4 * kWinCap;
-    static constexpr uint32_t iS0 = tCode + 4 * kWinCap;
+    static constexpr uint32_t tCode = tKey + 4 * wcap;
+    static constexpr uint32_t iS0 = tCode + 4 * wcap;
     static constexpr uint32_t iCs = iS0 + 4 * FC;
     static constexpr uint32_t iL0 = iCs + 4 * FC;
     static constexpr uint32_t iCl = iL0 + 4 * FC;
@@ -160,7 +162,8 @@ struct Ctx {
     unsigned long long* sB;
     Scr* scr;
     int32_t W, T, tid, lane, wid, nw;
-    int32_t FC;             // frontier records and implication slots in LDS: max(T, kFrontCap)
+    int32_t FC;             // frontier records and implication slots in LDS, at least T
+    int32_t wbits;          // log2 of the winner table's entries
     int32_t decision, fallback_after, learning;
     int32_t ext;            // extended search: several answer sets, restarts, activity,
                             // several conflicts learned per step (compile-time in k_search)
@@ -369,7 +372,7 @@ DEV unsigned long long alldec_word(int w, int cdl, int W) {
     return m << (a - b0);
 }
 
-DEV int tab_hash(int x) { return (int)(((uint32_t)x * 0x9E3779B1u) >> (32 - kWinBits)); }
+DEV int tab_hash(int x, int bits) { return (int)(((uint32_t)x * 0x9E3779B1u) >> (32 - bits)); }
 
 // Slot of variable x in the round's winner table (inserted if absent;
 // `first` is set for the one lane that inserted it); -1 when the probe
@@ -378,9 +381,9 @@ DEV int tab_hash(int x) { return (int)(((uint32_t)x * 0x9E3779B1u) >> (32 - kWin
 // a lane probing for x passes the same occupied slots as the lane that
 // inserted it, and a full window stays full.
 DEV int tab_insert(Ctx& c, int x, int& first) {
-    const int h = tab_hash(x);
+    const int h = tab_hash(x, c.wbits), mask = (1 << c.wbits) - 1;
     for (int p = 0; p < kWinProbe; ++p) {
-        const int sl = (h + p) & (kWinCap - 1);
+        const int sl = (h + p) & mask;
         const int old = atomicCAS(&c.tKey[sl], -1, x);
         if (old == -1) first = 1;
         if (old == -1 || old == x) return sl;
@@ -390,9 +393,9 @@ DEV int tab_insert(Ctx& c, int x, int& first) {
 
 // Slot of x once every insertion of the round is done; -1 if absent.
 DEV int tab_find(const Ctx& c, int x) {
-    const int h = tab_hash(x);
+    const int h = tab_hash(x, c.wbits), mask = (1 << c.wbits) - 1;
     for (int p = 0; p < kWinProbe; ++p) {
-        const int sl = (h + p) & (kWinCap - 1);
+        const int sl = (h + p) & mask;
         const int key = c.tKey[sl];
         if (key == x) return sl;
         if (key == -1) return -1;
@@ -401,7 +404,7 @@ DEV int tab_find(const Ctx& c, int x) {
 }
 
 DEV void tab_clear_all(Ctx& c) {
-    for (int i = c.tid; i < kWinCap; i += c.T) {
+    for (int i = c.tid; i < 1 << c.wbits; i += c.T) {
         c.tKey[i] = -1;
         c.tCode[i] = 0;
         c.tWin[i] = WIN_NONE;
@@ -1424,7 +1427,7 @@ __device__ __attribute__((noinline)) unsigned wave_run(LDSP Scr* scr_, LDSP unsi
                 const int xw = w ? x[1] : x[0];
                 int at = -1;
                 for (int p = 0; p < kWinProbe; ++p) {
-                    const int sl = (tab_hash(xw) + p) & (kWinCap - 1);
+                    const int sl = (tab_hash(xw, M::wbits) + p) & (M::wcap - 1);
                     int32_t was = -1;
                     __hip_atomic_compare_exchange_strong(&tKey[sl], &was, xw, __ATOMIC_RELAXED,
                                                          __ATOMIC_RELAXED,
@@ -2603,30 +2606,31 @@ __global__ __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu((EN == 0 &
     c.lane = threadIdx.x & 63;
     c.wid = threadIdx.x >> 6;
     c.nw = MAXT / 64;
-    c.FC = MAXT > kFrontCap ? MAXT : kFrontCap;
+    c.FC = a.fc;
+    c.wbits = win_bits(a.fc);
     c.scr = &scr;
     c.my_visits = c.my_checks = 0ull;
     {
-        typedef LdsMap<(MAXT > kFrontCap ? MAXT : kFrontCap)> M;
+        // the arrays of LdsMap<FC>
         unsigned char* p = (unsigned char*)smem16;
+        const size_t fc = (size_t)a.fc, wc = (size_t)1 << win_bits(a.fc);
         c.base = p;
-        c.sB = (unsigned long long*)(p + M::sB);
-        c.tWin = (unsigned long long*)(p + M::tWin);
-        c.iDeps = (unsigned long long*)(p + M::iDeps);
-        c.fDeps = (unsigned long long*)(p + M::fDeps);
-        c.tKey = (int32_t*)(p + M::tKey);
-        c.tCode = (int32_t*)(p + M::tCode);
-        c.iS0 = (int32_t*)(p + M::iS0);
-        c.iCs = (int32_t*)(p + M::iCs);
-        c.iL0 = (int32_t*)(p + M::iL0);
-        c.iCl = (int32_t*)(p + M::iCl);
-        c.fS0 = (int32_t*)(p + M::fS0);
-        c.fCs = (int32_t*)(p + M::fCs);
-        c.fL0 = (int32_t*)(p + M::fL0);
-        c.fCl = (int32_t*)(p + M::fCl);
-        c.fNew = (int32_t*)(p + M::fNew);
-        c.fSlot = (int32_t*)(p + M::fSlot);
-        p += M::end;
+        c.sB = (unsigned long long*)p; p += 8 * kMaxW;
+        c.tWin = (unsigned long long*)p; p += 8 * wc;
+        c.iDeps = (unsigned long long*)p; p += 8 * fc;
+        c.fDeps = (unsigned long long*)p; p += 8 * fc;
+        c.tKey = (int32_t*)p; p += 4 * wc;
+        c.tCode = (int32_t*)p; p += 4 * wc;
+        c.iS0 = (int32_t*)p; p += 4 * fc;
+        c.iCs = (int32_t*)p; p += 4 * fc;
+        c.iL0 = (int32_t*)p; p += 4 * fc;
+        c.iCl = (int32_t*)p; p += 4 * fc;
+        c.fS0 = (int32_t*)p; p += 4 * fc;
+        c.fCs = (int32_t*)p; p += 4 * fc;
+        c.fL0 = (int32_t*)p; p += 4 * fc;
+        c.fCl = (int32_t*)p; p += 4 * fc;
+        c.fNew = (int32_t*)p; p += 4 * fc;
+        c.fSlot = (int32_t*)p; p += 4 * fc;
         c.sTile = nullptr;   // Res-learning only
         if (LR == LEARN_RES) {
             c.sTile = (unsigned long long*)p;
@@ -2656,14 +2660,13 @@ __global__ __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu((EN == 0 &
 }
 
 // ------------------------------------------------------------ launchers
-size_t lds_bytes(int threads, int words, int awords, int owords, int learning) {
-    const size_t fc = threads > kFrontCap ? (size_t)threads : (size_t)kFrontCap;
+size_t lds_bytes(int threads, int fc, int words, int awords, int owords, int learning) {
+    const size_t f = (size_t)fc, wc = (size_t)1 << win_bits(fc);
     return sizeof(uint32_t) * ((size_t)words + (size_t)awords + (size_t)owords) +
-           sizeof(unsigned long long) * kMaxW +
-           sizeof(int32_t) * (size_t)threads + sizeof(int32_t) * 6 * fc +
-           (sizeof(unsigned long long) + 2 * sizeof(int32_t)) * (size_t)kWinCap +
-           (sizeof(unsigned long long) + 4 * sizeof(int32_t)) * fc +
-           sizeof(unsigned long long) * (fc + (learning == LEARN_RES ? (size_t)threads : 0));
+           sizeof(unsigned long long) * kMaxW + sizeof(int32_t) * (size_t)threads +
+           (sizeof(unsigned long long) + 2 * sizeof(int32_t)) * wc +
+           (2 * sizeof(unsigned long long) + 10 * sizeof(int32_t)) * f +
+           sizeof(unsigned long long) * (learning == LEARN_RES ? (size_t)threads : 0);
 }
 
 template <int LR, int EN>

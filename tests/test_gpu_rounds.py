@@ -65,6 +65,18 @@ def test_round_edges(P, width, per_atom, threads):
             break
 
 
+@pytest.mark.parametrize("threads", [64, 256])
+@pytest.mark.parametrize("width,per_atom", [(255, 1), (256, 1), (257, 1), (511, 2), (512, 2),
+                                            (513, 2), (1023, 10), (1024, 10), (1025, 10)])
+def test_record_edges(P, width, per_atom, threads):
+    """Rounds that imply as many variables as LDS holds records for (256 below
+    4096 variables, 512 below 32768, then 1024), one fewer, and one more."""
+    prog = fan(width, per_atom)
+    for n in (3, 4, 5, 6, 7, 8, 12, 40):
+        if not _compare(P, prog, n, threads):
+            break
+
+
 @pytest.mark.parametrize("learning", [0, 1])
 @pytest.mark.parametrize("seed", range(6))
 def test_learned_visits(P, seed, learning):
