@@ -21,9 +21,19 @@
 // per-edge products and no atomics.  The epilogue multiplies the tile's own
 // rows by the self matrix, adds the normalised edge term and the bias,
 // requantises, and stores the 64 codes per row.
+//
+// What bounds a layer kernel is the conversions around the products (a limb of
+// 32 sums per thread, the requantisation of 16 elements), then the gathers:
+// on 512 programs of 100..5000 atoms (17M nogood rows, 38M edges) a nogood
+// kernel took 3.95 ms with limbs selected by a loop's shift and 64-bit
+// recombination for every tile, 2.6 ms with the byte selected at compile time,
+// 32 bits wherever the sums are below 2^16, and the tile's own rows loaded
+// ahead of the edges; a variable kernel 2.99 and 1.9 ms.
 #include <hip/hip_runtime.h>
 #include <stddef.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 #include "../../include/asp.h"
 #include "scorer.h"
@@ -50,13 +60,15 @@ DEV int bf16_int(uint16_t b) { return (int)__uint_as_float((uint32_t)b << 16); }
 // Activation code 0..255 as bfloat16 bits (exact).
 DEV uint16_t code_bf16(uint32_t code) { return (uint16_t)(__float_as_uint((float)code) >> 16); }
 
-DEV int act(long long z) { return z <= 0 ? 0 : (int)(((z + 256) >> 9) < 255 ? ((z + 256) >> 9) : 255); }
+template <class T>
+DEV int act(T z) { return z <= 0 ? 0 : (int)(((z + 256) >> 9) < 255 ? ((z + 256) >> 9) : 255); }
 
 // s / 2^k rounded half up (arithmetic shift), k = ceil(log2 n); n <= 1: s.
-DEV long long norm_sum(long long s, int n) {
+template <class T>
+DEV T norm_sum(T s, int n) {
     if (n <= 1) return s;
     const int k = 32 - __clz(n - 1);
-    return (s + (1LL << (k - 1))) >> k;
+    return (s + ((T)1 << (k - 1))) >> k;
 }
 
 // One 32x32 block: 32 rows of an operand tile (stride LD) times 32 output
@@ -119,19 +131,13 @@ DEV void stage_t2(uint16_t* BT, const uint16_t* M0, const uint16_t* M1, int tid)
     }
 }
 
-// 16 activation codes from global memory as bfloat16 into an operand row.
-DEV void load_codes16(uint16_t* dst, const uint8_t* src) {
-    const uint4 q = *(const uint4*)src;
+// 16 activation codes as bfloat16 into an operand row.
+DEV void codes16(uint16_t* dst, const uint4 q) {
     const uint32_t w[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
     for (int b = 0; b < 4; ++b)
 #pragma unroll
         for (int t = 0; t < 4; ++t) dst[4 * b + t] = code_bf16((w[b] >> (8 * t)) & 255u);
-}
-
-DEV void zero16(uint16_t* dst) {
-#pragma unroll
-    for (int t = 0; t < 16; ++t) dst[t] = 0;
 }
 
 // 16 codes (bytes of a row quarter) added into 16 integer sums.
@@ -174,29 +180,42 @@ DEV LayerLds carve(unsigned char* p) {
 // is linear, so this equals the sum of every edge's own product.  The sums
 // (up to 255 per edge) are split into base-256 limbs, each exact in
 // bfloat16; a limb's product (|.| <= 255 * 127 * 2H < 2^24) is exact in the
-// float32 accumulator, and the limbs recombine in 64-bit integers.  Returns
-// this lane's 16 elements of its wave's 32x32 output block.
+// float32 accumulator, and the limbs recombine in integers.  edge_sums returns
+// the number of limbs that the tile's largest sum needs; edge_term this lane's
+// 16 elements of its wave's 32x32 output block.
 template <class Edges>
-DEV void edge_term(const LayerLds& L, int rows, Edges edges, int tid, long long* tot) {
+DEV int edge_sums(const LayerLds& L, int rows, Edges edges, int tid, int* sp, int* sn) {
     const int w = tid >> 6, lane = tid & 63;
     const int r = 16 * w + (lane >> 2), q = lane & 3;
-    int sp[16], sn[16];
 #pragma unroll
     for (int t = 0; t < 16; ++t) sp[t] = sn[t] = 0;
     if (r < rows) edges(r, q, sp, sn);
     int mx = 0;
 #pragma unroll
     for (int t = 0; t < 16; ++t) mx = max(mx, max(sp[t], sn[t]));
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) mx = max(mx, __shfl_xor(mx, d, 64));
     if (tid == 0) *L.smax = 0;
     __syncthreads();
-    atomicMax(L.smax, mx);
+    if (lane == 0) atomicMax(L.smax, mx);
     __syncthreads();
     const int top = *L.smax;
-    const int nl = top < (1 << 8) ? 1 : top < (1 << 16) ? 2 : top < (1 << 24) ? 3 : 4;
+    return top < (1 << 8) ? 1 : top < (1 << 16) ? 2 : top < (1 << 24) ? 3 : 4;
+}
+
+// MOST: the most limbs there can be.  Two (sums below 2^16, almost every tile)
+// recombine in 32 bits: |tot| <= 65535 * 127 * 2H < 2^31 (and half of that, or
+// at most one edge's product, once normalised; the biases are within 2^24).
+template <int MOST, class T>
+DEV void edge_term(const LayerLds& L, int nl, const int* sp, const int* sn, int tid, T* tot) {
+    const int w = tid >> 6, lane = tid & 63;
+    const int r = 16 * w + (lane >> 2), q = lane & 3;
     const int rb = w & 1, cb = w >> 1;
 #pragma unroll
     for (int t = 0; t < 16; ++t) tot[t] = 0;
-    for (int li = 0; li < nl; ++li) {
+#pragma unroll
+    for (int li = 0; li < MOST; ++li) {
+        if (li >= nl) break;
         uint16_t* row = L.opa + r * LD2 + 16 * q;
 #pragma unroll
         for (int t = 0; t < 16; ++t) {
@@ -206,7 +225,7 @@ DEV void edge_term(const LayerLds& L, int rows, Edges edges, int tid, long long*
         __syncthreads();
         const v16f o = mma_block2(L.opa + 32 * rb * LD2, L.wt + 32 * cb * LD2, lane);
 #pragma unroll
-        for (int t = 0; t < 16; ++t) tot[t] += (long long)(int)o[t] * (1LL << (8 * li));
+        for (int t = 0; t < 16; ++t) tot[t] += (T)(int)o[t] * ((T)1 << (8 * li));
         __syncthreads();
     }
 }
@@ -215,25 +234,47 @@ DEV void edge_term(const LayerLds& L, int rows, Edges edges, int tid, long long*
 // self matrix, plus the normalised edge term and the bias, requantised into
 // `out` rows.  seg_len(row) gives the normaliser; rows >= rows_n are not
 // written.
-template <class Len>
-DEV void finish_tile(const LayerLds& L, int rows_n, Len seg_len, int zero_row, const long long* tot,
+template <class T, class Len>
+DEV void finish_tile(const LayerLds& L, int rows_n, Len seg_len, int zero_row, const T* tot,
                      uint8_t* out, int tid) {
     const int w = tid >> 6, lane = tid & 63;
     const int rb = w & 1, cb = w >> 1;
     const v16f o = mma_block(L.opa + 32 * rb * LD, L.st + 32 * cb * LD, lane);
     __syncthreads();                               // operand tile is read; codes may alias it
     uint8_t* codes = (uint8_t*)L.opa;
+    const int col = 32 * cb + (lane & 31);
+    const int bias = L.bias[col];
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-        const int row = 32 * rb + blk_row(r, lane), col = 32 * cb + (lane & 31);
+        const int row = 32 * rb + blk_row(r, lane);
         if (row < rows_n) {
-            const long long z = (long long)(int)o[r] + norm_sum(tot[r], seg_len(row)) + L.bias[col];
+            const T z = (T)(int)o[r] + norm_sum(tot[r], seg_len(row)) + (T)bias;
             codes[row * H + col] = row == zero_row ? (uint8_t)0 : (uint8_t)act(z);
         }
     }
     __syncthreads();
     const int row = tid >> 2, part = tid & 3;
     if (row < rows_n) *(uint4*)(out + (size_t)row * H + part * 16) = *(const uint4*)(codes + row * H + part * 16);
+}
+
+// A tile's update from its edge sums and its own rows (own: 16 codes of row
+// tid / 4, loaded before the edges were gathered).
+template <class Len>
+DEV void update_tile(const LayerLds& L, int rows, int nl, const int* sp, const int* sn, const uint4 own,
+                     Len seg_len, int zero_row, uint8_t* out, int tid) {
+    auto run = [&](auto* tot, auto most) {
+        edge_term<decltype(most)::value>(L, nl, sp, sn, tid, tot);
+        codes16(L.opa + (tid >> 2) * LD + (tid & 3) * 16, own);
+        __syncthreads();
+        finish_tile(L, rows, seg_len, zero_row, tot, out, tid);
+    };
+    if (nl <= 2) {
+        int tot[16];
+        run(tot, std::integral_constant<int, 2>());
+    } else {
+        long long tot[16];
+        run(tot, std::integral_constant<int, 4>());
+    }
 }
 
 // ------------------------------------------------------------------ kernels
@@ -293,9 +334,9 @@ __global__ __launch_bounds__(NT) void k_embed(ScorerArgs a) {
             const bool zero = var && tl.row0 + row == 0;
             uint32_t pk[4] = {0u, 0u, 0u, 0u};
             for (int j = 0; j < 16; ++j) {
-                long long z = sB[c0 + j];
+                int z = sB[c0 + j];                  // within 2^24 + 8 * 255 * 127
 #pragma unroll
-                for (int f = 0; f < F; ++f) z += (long long)sX[row][f] * sE[f * H + c0 + j];
+                for (int f = 0; f < F; ++f) z += __mul24(sX[row][f], sE[f * H + c0 + j]);
                 const uint32_t code = zero ? 0u : (uint32_t)act(z);
                 pk[j >> 2] |= code << (8 * (j & 3));
             }
@@ -306,7 +347,8 @@ __global__ __launch_bounds__(NT) void k_embed(ScorerArgs a) {
 }
 
 // Nogood update of layer l: hc = act(hc S + norm(sum hv P | hv N, |c|) + bc).
-__global__ __launch_bounds__(NT) void k_nogoods(ScorerArgs a, int l) {
+// (three waves per SIMD: the workgroups that the LDS holds)
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(3))) void k_nogoods(ScorerArgs a, int l) {
     HIP_DYNAMIC_SHARED(uint4, smem16);   // 16-byte aligned base for the bf16 operand rows
     const LayerLds L = carve((unsigned char*)smem16);
     const int tid = threadIdx.x;
@@ -324,9 +366,12 @@ __global__ __launch_bounds__(NT) void k_nogoods(ScorerArgs a, int l) {
         const uint8_t* hv = a.ws + a.hv_off[tl.inst];
         uint8_t* hc = a.ws + a.hc_off[tl.inst] + (size_t)tl.row0 * H;
         for (int i = tid; i <= rows; i += NT) L.start[i] = NO[i];
+        const int er = tid >> 2, part = tid & 3;
+        uint4 own = make_uint4(0u, 0u, 0u, 0u);
+        if (er < rows) own = *(const uint4*)(hc + (size_t)er * H + part * 16);
         __syncthreads();
-        long long tot[16];
-        edge_term(L, rows, [&](int r, int q, int* sp, int* sn) {
+        int sp[16], sn[16];
+        const int nl = edge_sums(L, rows, [&](int r, int q, int* sp, int* sn) {
             const int e1 = L.start[r + 1];
             for (int e = L.start[r]; e < e1; e += 2) {
                 const bool two = e + 1 < e1;
@@ -337,19 +382,15 @@ __global__ __launch_bounds__(NT) void k_nogoods(ScorerArgs a, int l) {
                 if (l0 > 0) add_codes16(sp, c0); else add_codes16(sn, c0);
                 if (l1 > 0) add_codes16(sp, c1); else add_codes16(sn, c1);
             }
-        }, tid, tot);
-        const int er = tid >> 2, part = tid & 3;
-        if (er < rows) load_codes16(L.opa + er * LD + part * 16, hc + (size_t)er * H + part * 16);
-        else zero16(L.opa + er * LD + part * 16);
-        __syncthreads();
-        finish_tile(L, rows, [&](int row) { return L.start[row + 1] - L.start[row]; }, -1, tot, hc, tid);
+        }, tid, sp, sn);
+        update_tile(L, rows, nl, sp, sn, own, [&](int row) { return L.start[row + 1] - L.start[row]; }, -1, hc, tid);
         __syncthreads();
     }
 }
 
 // Variable update of layer l: hv = act(hv T + norm(sum hc Q | hc R, deg v) + bv);
 // the last layer also writes each atom's score hv . wo + bo.
-__global__ __launch_bounds__(NT) void k_vars(ScorerArgs a, int l, int last) {
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(3))) void k_vars(ScorerArgs a, int l, int last) {
     HIP_DYNAMIC_SHARED(uint4, smem16);   // 16-byte aligned base for the bf16 operand rows
     const LayerLds L = carve((unsigned char*)smem16);
     __shared__ int sWo[H];
@@ -373,10 +414,13 @@ __global__ __launch_bounds__(NT) void k_vars(ScorerArgs a, int l, int last) {
         uint8_t* hv = a.ws + a.hv_off[tl.inst] + (size_t)tl.row0 * H;
         const int nseg = 2 * rows;
         for (int i = tid; i <= nseg; i += NT) L.start[i] = MO[i];
+        const int er = tid >> 2, part = tid & 3;
+        uint4 own = make_uint4(0u, 0u, 0u, 0u);
+        if (er < rows) own = *(const uint4*)(hv + (size_t)er * H + part * 16);
         __syncthreads();
-        long long tot[16];
+        int sp[16], sn[16];
         // a variable's positive literal's occurrences, then its negative's
-        edge_term(L, rows, [&](int r, int q, int* sp, int* sn) {
+        const int nl = edge_sums(L, rows, [&](int r, int q, int* sp, int* sn) {
             const int e1 = L.start[2 * r + 2], em = L.start[2 * r + 1];
             for (int e = L.start[2 * r]; e < e1; e += 2) {
                 const bool two = e + 1 < e1;
@@ -387,13 +431,9 @@ __global__ __launch_bounds__(NT) void k_vars(ScorerArgs a, int l, int last) {
                 if (e < em) add_codes16(sp, x0); else add_codes16(sn, x0);
                 if (e + 1 < em) add_codes16(sp, x1); else add_codes16(sn, x1);
             }
-        }, tid, tot);
-        const int er = tid >> 2, part = tid & 3;
-        if (er < rows) load_codes16(L.opa + er * LD + part * 16, hv + (size_t)er * H + part * 16);
-        else zero16(L.opa + er * LD + part * 16);
-        __syncthreads();
-        finish_tile(L, rows, [&](int row) { return L.start[2 * row + 2] - L.start[2 * row]; },
-                    tl.row0 == 0 ? 0 : -1, tot, hv, tid);
+        }, tid, sp, sn);
+        update_tile(L, rows, nl, sp, sn, own, [&](int row) { return L.start[2 * row + 2] - L.start[2 * row]; },
+                    tl.row0 == 0 ? 0 : -1, hv, tid);
         if (last && tid < rows) {
             const int v = tl.row0 + tid;
             if (v <= d.A) {
