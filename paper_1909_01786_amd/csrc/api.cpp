@@ -24,7 +24,7 @@
 #include "train.h"
 
 namespace asp {
-size_t lds_bytes(int threads, int fc, int words, int awords, int owords, int learning);
+size_t lds_bytes(int threads, int fc, int wbits, int words, int awords, int owords, int learning);
 hipError_t launch_search(const KArgs& a, int threads, int grid, size_t lds, hipStream_t s);
 hipError_t set_max_lds(int threads, size_t lds);
 }  // namespace asp
@@ -82,7 +82,7 @@ bool valid_threads(int t) { return t == 64 || t == 128 || t == 256 || t == 512 |
 // One launch of the search kernel: instances order[first .. first+count),
 // LDS sized for the largest of them.
 struct LaunchClass {
-    int32_t first = 0, count = 0, words = 1, awords = 1, owords = 0, threads = 128, fc = 128;
+    int32_t first = 0, count = 0, words = 1, awords = 1, owords = 0, threads = 128, fc = 128, wbits = 8;
     size_t lds = 0;
 };
 
@@ -296,8 +296,18 @@ int32_t make_plan(const std::vector<const HostProgram*>& progs, const asp_option
         lc.owords = P.learning == ASP_LEARN_FWD ? (int32_t)((omax + 1 + 31) / 32) : 0;
         const int32_t least = std::max(lc.threads, 128);
         lc.fc = std::max(least, front_records(vmax));
-        auto fit = [&] { lc.lds = lds_bytes(lc.threads, lc.fc, lc.words, lc.awords, lc.owords, P.learning); };
-        for (fit(); lc.lds > kLdsPerGroup && lc.fc > least; fit()) lc.fc /= 2;
+        // (twice as many winner-table entries as records, 256 at least; what
+        // needs all the LDS gets one record per thread and 256 entries)
+        lc.wbits = lc.fc <= 128 ? 8 : lc.fc <= 256 ? 9 : lc.fc <= 512 ? 10 : 11;
+        auto fit = [&] { lc.lds = lds_bytes(lc.threads, lc.fc, lc.wbits, lc.words, lc.awords, lc.owords, P.learning); };
+        for (fit(); lc.lds > kLdsPerGroup && lc.fc > least; fit()) {
+            lc.fc /= 2;
+            lc.wbits -= 1;
+        }
+        if (lc.lds > kLdsPerGroup) {
+            lc.wbits = 8;
+            fit();
+        }
         if (lc.lds > kLdsPerGroup) {
             lc.owords = 0;
             fit();
@@ -417,6 +427,7 @@ KArgs make_args(const Plan& P, uint8_t* arena, int32_t mode, const LaunchClass& 
     a.awords = lc.awords;
     a.owords = lc.owords;
     a.fc = lc.fc;
+    a.wbits = lc.wbits;
     a.step_mask = 0;
     a.max_steps = -1;
     a.max_conflicts = -1;

@@ -205,6 +205,7 @@ struct KArgs {
     int32_t awords;              // LDS words of the 1-bit atom map (this launch's largest A)
     int32_t owords;              // LDS words of the learned-occurrence bits, 0 without them
     int32_t fc;                  // LDS frontier records (128, 256, 512 or 1024; at least one per thread)
+    int32_t wbits, pad2;         // log2 of the LDS winner table's entries
 };
 
 }  // namespace asp

@@ -50,11 +50,6 @@ constexpr uint32_t NO_ENTRY = 0xffffffffu;      // implier without a map entry (
 constexpr uint64_t FNV_BASIS = 1469598103934665603ull;
 constexpr uint64_t FNV_PRIME = 1099511628211ull;
 constexpr int kMaxWaves = 16;
-// Entries of the LDS winner table (variables implied in a round) for FC
-// frontier records and implication slots.
-__host__ __device__ constexpr int win_bits(int fc) {
-    return fc <= 128 ? 8 : fc <= 256 ? 9 : fc <= 512 ? 10 : 11;
-}
 constexpr int kWinProbe = 32;
 constexpr uint32_t SLOT_TAG = 0x80000000u;
 constexpr int kLitBatch = 4;     // literals of a long nogood loaded together in a visit
@@ -104,14 +99,10 @@ struct Scr {
 // frontier records and implication slots.  The per-instance maps follow.
 template <int FC>
 struct LdsMap {
-    static constexpr int wbits = win_bits(FC), wcap = 1 << wbits;
     static constexpr uint32_t sB = 0;
-    static constexpr uint32_t tWin = sB + 8 * kMaxW;
-    static constexpr uint32_t iDeps = tWin + 8 * wcap;
+    static constexpr uint32_t iDeps = sB + 8 * kMaxW;
     static constexpr uint32_t fDeps = iDeps + 8 * FC;
-    static constexpr uint32_t tKey = fDeps + 8 * FC;
-    static constexpr uint32_t tCode = tKey + 4 * wcap;
-    static constexpr uint32_t iS0 = tCode + 4 * wcap;
+    static constexpr uint32_t iS0 = fDeps + 8 * FC;
     static constexpr uint32_t iCs = iS0 + 4 * FC;
     static constexpr uint32_t iL0 = iCs + 4 * FC;
     static constexpr uint32_t iCl = iL0 + 4 * FC;
@@ -121,7 +112,7 @@ struct LdsMap {
     static constexpr uint32_t fCl = fL0 + 4 * FC;
     static constexpr uint32_t fNew = fCl + 4 * FC;
     static constexpr uint32_t fSlot = fNew + 4 * FC;
-    static constexpr uint32_t end = fSlot + 4 * FC;
+    static constexpr uint32_t tWin = fSlot + 4 * FC;   // then tKey and tCode, by the table's size
 };
 
 struct Ctx {
@@ -1154,8 +1145,9 @@ template <int FC, bool RES>
 __device__ __attribute__((noinline)) unsigned wave_run(LDSP Scr* scr_, LDSP unsigned char* base_,
                                                        uint32_t valb_, uint32_t occ_, int qh, int qt,
                                                        int A, int nS, int cdl, int max_rounds,
-                                                       int multi) {
+                                                       int multi, int wbits) {
     typedef LdsMap<FC> M;
+    wbits = uni(wbits);
     LDSP Scr* s = (LDSP Scr*)(uintptr_t)uni((int)(uintptr_t)scr_);
     LDSP unsigned char* base = (LDSP unsigned char*)(uintptr_t)uni((int)(uintptr_t)base_);
     const uint32_t occ = (uint32_t)uni((int)occ_);
@@ -1164,7 +1156,7 @@ __device__ __attribute__((noinline)) unsigned wave_run(LDSP Scr* scr_, LDSP unsi
     LDSP unsigned long long* tWin = (LDSP unsigned long long*)(base + M::tWin);
     LDSP unsigned long long* fDeps = (LDSP unsigned long long*)(base + M::fDeps);
     LDSP uint32_t* filt = (LDSP uint32_t*)(base + M::iDeps);
-    LDSP int32_t* tKey = (LDSP int32_t*)(base + M::tKey);
+    LDSP int32_t* tKey = (LDSP int32_t*)(base + M::tWin + (8u << wbits));
     LDSP int32_t* mk = (LDSP int32_t*)(base + M::iS0);    // visit-run marks
     LDSP int32_t* fS0 = (LDSP int32_t*)(base + M::fS0);
     LDSP int32_t* fCs = (LDSP int32_t*)(base + M::fCs);
@@ -1427,7 +1419,7 @@ __device__ __attribute__((noinline)) unsigned wave_run(LDSP Scr* scr_, LDSP unsi
                 const int xw = w ? x[1] : x[0];
                 int at = -1;
                 for (int p = 0; p < kWinProbe; ++p) {
-                    const int sl = (tab_hash(xw, M::wbits) + p) & (M::wcap - 1);
+                    const int sl = (tab_hash(xw, wbits) + p) & ((1 << wbits) - 1);
                     int32_t was = -1;
                     __hip_atomic_compare_exchange_strong(&tKey[sl], &was, xw, __ATOMIC_RELAXED,
                                                          __ATOMIC_RELAXED,
@@ -1549,8 +1541,8 @@ DEV int wave_rounds(Ctx& c, Ctl& k, int max_rounds) {
         const uint32_t oo = c.occb ? (uint32_t)((unsigned char*)c.occb - c.base) : 0u;
         const int multi = c.multi && c.learn_k > 1 ? 1 : 0;
         const unsigned ch = c.learning == LEARN_RES
-            ? wave_run<FC, true>((LDSP Scr*)c.scr, base, vo, oo, k.qh, k.qt, k.A, k.nS, k.cdl, max_rounds, multi)
-            : wave_run<FC, false>((LDSP Scr*)c.scr, base, vo, oo, k.qh, k.qt, k.A, k.nS, k.cdl, max_rounds, multi);
+            ? wave_run<FC, true>((LDSP Scr*)c.scr, base, vo, oo, k.qh, k.qt, k.A, k.nS, k.cdl, max_rounds, multi, c.wbits)
+            : wave_run<FC, false>((LDSP Scr*)c.scr, base, vo, oo, k.qh, k.qt, k.A, k.nS, k.cdl, max_rounds, multi, c.wbits);
         c.my_checks += (unsigned long long)ch;
     }
     bar();
@@ -2607,20 +2599,17 @@ __global__ __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu((EN == 0 &
     c.wid = threadIdx.x >> 6;
     c.nw = MAXT / 64;
     c.FC = a.fc;
-    c.wbits = win_bits(a.fc);
+    c.wbits = a.wbits;
     c.scr = &scr;
     c.my_visits = c.my_checks = 0ull;
     {
         // the arrays of LdsMap<FC>
         unsigned char* p = (unsigned char*)smem16;
-        const size_t fc = (size_t)a.fc, wc = (size_t)1 << win_bits(a.fc);
+        const size_t fc = (size_t)a.fc, wc = (size_t)1 << a.wbits;
         c.base = p;
         c.sB = (unsigned long long*)p; p += 8 * kMaxW;
-        c.tWin = (unsigned long long*)p; p += 8 * wc;
         c.iDeps = (unsigned long long*)p; p += 8 * fc;
         c.fDeps = (unsigned long long*)p; p += 8 * fc;
-        c.tKey = (int32_t*)p; p += 4 * wc;
-        c.tCode = (int32_t*)p; p += 4 * wc;
         c.iS0 = (int32_t*)p; p += 4 * fc;
         c.iCs = (int32_t*)p; p += 4 * fc;
         c.iL0 = (int32_t*)p; p += 4 * fc;
@@ -2631,6 +2620,9 @@ __global__ __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu((EN == 0 &
         c.fCl = (int32_t*)p; p += 4 * fc;
         c.fNew = (int32_t*)p; p += 4 * fc;
         c.fSlot = (int32_t*)p; p += 4 * fc;
+        c.tWin = (unsigned long long*)p; p += 8 * wc;
+        c.tKey = (int32_t*)p; p += 4 * wc;
+        c.tCode = (int32_t*)p; p += 4 * wc;
         c.sTile = nullptr;   // Res-learning only
         if (LR == LEARN_RES) {
             c.sTile = (unsigned long long*)p;
@@ -2660,8 +2652,8 @@ __global__ __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu((EN == 0 &
 }
 
 // ------------------------------------------------------------ launchers
-size_t lds_bytes(int threads, int fc, int words, int awords, int owords, int learning) {
-    const size_t f = (size_t)fc, wc = (size_t)1 << win_bits(fc);
+size_t lds_bytes(int threads, int fc, int wbits, int words, int awords, int owords, int learning) {
+    const size_t f = (size_t)fc, wc = (size_t)1 << wbits;
     return sizeof(uint32_t) * ((size_t)words + (size_t)awords + (size_t)owords) +
            sizeof(unsigned long long) * kMaxW + sizeof(int32_t) * (size_t)threads +
            (sizeof(unsigned long long) + 2 * sizeof(int32_t)) * wc +
