@@ -1284,7 +1284,10 @@ int32_t asp_state_import(asp_program* p, void* stream, const asp_state* st) {
     HIPCHK(put(L.ctrl, &k, sizeof(k)));
     HIPCHK(put(L.val8, st->val, (size_t)V + 1));
     HIPCHK(put(L.lvl, lvl.data(), 4 * lvl.size()));
-    HIPCHK(put(L.deps, st->deps, 8 * ((size_t)V + 1) * W));
+    // no variable is 0: its Deps are read for a nogood's absent literals, and empty
+    const std::vector<uint64_t> none((size_t)W, 0ull);
+    HIPCHK(put(L.deps, none.data(), 8 * none.size()));
+    HIPCHK(put(L.deps + 8 * (int64_t)W, st->deps + W, 8 * (size_t)V * W));
     HIPCHK(put(L.win, win.data(), 8 * win.size()));
     HIPCHK(put(L.trail, trail.data(), 4 * trail.size()));
     HIPCHK(put(L.tlim, tlim.data(), 4 * tlim.size()));

@@ -5,12 +5,13 @@ the others to the general round; single steps never start one (the frontier
 records are in LDS only between the steps of one launch), so each program is
 run from the start for n steps at once and the whole state is compared.
 """
+import numpy as np
 import pytest
 import torch  # noqa: F401  (loads the HIP runtime the library uses)
 
 import aspgen
 import oracle
-from parity import STATUS, assert_same_state, assert_same_stats
+from parity import STATUS, assert_same_state, assert_same_stats, to_lib_state
 
 pytestmark = pytest.mark.gpu
 
@@ -100,3 +101,28 @@ def test_ordered_candidates(P, lookahead, decision, threads):
                                     limits=oracle.make_limits(60))
         assert rc == STATUS[orc], prog.name
         assert_same_stats(ost, st, prog.name)
+
+
+@pytest.mark.parametrize("steps", [2, 40, 300])
+@pytest.mark.parametrize("seed", range(4))
+def test_import_ignores_variable_0(P, seed, steps):
+    """The arrays of an imported state have an entry 0 that belongs to no
+    variable: whatever a caller leaves there, the search goes on the same."""
+    prog = aspgen.single_random(1000 + seed)
+    o = oracle.Solver(prog)
+    while o.stats()["decisions"] < 3:
+        o.step()
+    st = to_lib_state(o.state(), o.stats())
+    st.val[0], st.deps[0] = 1, np.uint64(2 ** 64 - 1)
+    g = P.Program(prog).bind("cuda", threads=128)
+    g.import_state(st)
+    for _ in range(steps):
+        if o.next_step() == oracle.ST_DONE:
+            break
+        o.step()
+    rc, gst = g.run_steps(steps, P.limits(-1, 30000))
+    s = o.state()
+    assert rc == STATUS[s.status]
+    if s.status == oracle.RUNNING:
+        assert_same_state(s, g.export_state(), (seed, steps))
+    assert_same_stats(o.stats(), gst, (seed, steps))
