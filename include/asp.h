@@ -416,6 +416,13 @@ int32_t asp_batch_last_ms(asp_batch *batch, double *ms);
 int32_t asp_batch_launch_info(asp_batch *batch, int32_t *n_classes, int32_t *first,
                               int32_t *count, int32_t *threads, double *ms, int32_t *order);
 
+/* How launch c (as above) uses a CU's LDS: dynamic LDS bytes per workgroup,
+ * frontier records and winner-table entries in it, and the searches that a CU
+ * holds at once by its LDS and wave slots.  Arrays of 4 entries; any may be
+ * NULL.  Needs no device. */
+int32_t asp_batch_launch_lds(const asp_batch *batch, int32_t *per_cu, int64_t *lds,
+                             int32_t *records, int32_t *table);
+
 int32_t asp_batch_free(asp_batch *batch);
 
 /* Scores of a batch instance i (see asp_set_scores / asp_get_scores). */

@@ -197,7 +197,7 @@ EXPORTS = (
     "asp_status_str", "asp_last_error", "asp_set_scores", "asp_get_scores",
     "asp_batch_set_scores", "asp_batch_get_scores", "asp_scorer_workspace",
     "asp_batch_scorer_workspace", "asp_score_program", "asp_score_batch",
-    "asp_batch_train_readout", "asp_batch_launch_info", "asp_solve_batch_graph",
+    "asp_batch_train_readout", "asp_batch_launch_info", "asp_batch_launch_lds", "asp_solve_batch_graph",
     "asp_get_models", "asp_solve_noalloc", "asp_scorer_train_workspace", "asp_scorer_train",
     "asp_scorer_quantize", "asp_scorer_dequantize", "asp_batch_learned",
 )
@@ -236,6 +236,7 @@ def lib():
             "asp_batch_results": (i32, [P, P, P, P, P]),
             "asp_batch_last_ms": (i32, [P, C.POINTER(C.c_double)]),
             "asp_batch_launch_info": (i32, [P, C.POINTER(i32), P, P, P, P, P]),
+            "asp_batch_launch_lds": (i32, [P, P, P, P, P]),
             "asp_batch_free": (i32, [P]),
             "asp_status_str": (C.c_char_p, [i32]),
             "asp_last_error": (i32, [C.c_char_p, u64]),
@@ -597,6 +598,16 @@ class Batch:
         order = np.zeros(len(self.programs), np.int32)
         _check(lib().asp_batch_launch_info(self._h, C.byref(n), first, count, thr, ms, _ptr(order)))
         return [(first[c], count[c], thr[c], ms[c]) for c in range(n.value)], order
+
+    def launch_lds(self):
+        """[(searches per CU, LDS bytes, frontier records, winner-table
+        entries)] per launch class."""
+        n = C.c_int32(0)
+        _check(lib().asp_batch_launch_info(self._h, C.byref(n), None, None, None, None, None))
+        held, rec, tab = (C.c_int32 * 4)(), (C.c_int32 * 4)(), (C.c_int32 * 4)()
+        lds = (C.c_int64 * 4)()
+        _check(lib().asp_batch_launch_lds(self._h, held, lds, rec, tab))
+        return [(held[c], lds[c], rec[c], tab[c]) for c in range(n.value)]
 
     def last_ms(self) -> float:
         ms = C.c_double(0)

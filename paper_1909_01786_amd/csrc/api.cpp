@@ -83,11 +83,13 @@ bool valid_threads(int t) { return t == 64 || t == 128 || t == 256 || t == 512 |
 // LDS sized for the largest of them.
 struct LaunchClass {
     int32_t first = 0, count = 0, words = 1, awords = 1, owords = 0, threads = 128, fc = 128, wbits = 8;
+    int64_t vsum = 0;                   // variables of its programs
     size_t lds = 0;
 };
 
 struct Plan {
     int32_t n = 0, threads = 256, W = 1, gate = 0, decision = 0, fallback_after = 10, learning = 0;
+    double Vtop = 0;                    // mean variables of the largest sixteenth
     int64_t Vmax = 0, Rhmax = 0, cap_ng = 0, cap_lits = 0;
     int64_t max_models = 1, restart_every = 0, model_store = 1;
     int32_t learn_k = 1;
@@ -183,15 +185,16 @@ asp_options default_options() {
 // LDS a workgroup can hold on gfx950 (static part included).
 constexpr size_t kLdsPerGroup = 160 * 1024 - 1024;
 
-// Frontier records and implication slots a workgroup keeps in LDS (and half
-// its winner table).  A round that implies more variables finds the rest's
+// The MI355X: compute units, LDS of one, and an allowance for a search's
+// static LDS (its Scr) and the allocation granularity.
+constexpr int32_t kCUs = 256;
+constexpr size_t kLdsPerCu = 160 * 1024, kLdsStatic = 512;
+
+// Frontier records and implication slots a workgroup has use for in LDS, by
+// its largest program.  A round that implies more variables finds the rest's
 // Deps, map segments and learned lists in memory again, five dependent
-// gathers for each thread's share, and the next one cannot start from LDS.
-// The larger programs' rounds in the middle of a cascade imply hundreds; with
-// 128 records (one per thread) a pass of 1024 random programs of 100..5000
-// atoms took 370 ms, so 315; a 2000-vertex colouring 49 and 45.5 ms (256
-// records, and 512).  Below 4096 variables 256 do, and leave the LDS to eight
-// workgroups a CU.
+// gathers for each thread's share, and the next one cannot start from LDS;
+// the larger programs' rounds in the middle of a cascade imply hundreds.
 int32_t front_records(int64_t V) { return V <= 4095 ? 256 : V <= 32767 ? 512 : 1024; }
 
 // LDS size classes by variable count (the 2-bit maps take V/4 bytes each).
@@ -201,6 +204,85 @@ std::vector<int64_t> class_bounds(int32_t classes) {
     case 2: return {16383};
     case 3: return {8191, 32767};
     default: return {4095, 16383, 32767};
+    }
+}
+
+// Searches of a class that a CU holds: by its LDS, and by its wave slots
+// (four waves per SIMD in the plain search with Fwd-learning, else three).
+int32_t per_cu(const Plan& P, const LaunchClass& lc) {
+    const bool plain = P.learning == ASP_LEARN_FWD && P.learn_k <= 1 && P.lookahead <= 1 &&
+                       P.max_models == 1 && P.restart_every == 0 && P.decision != ASP_DECISION_ACTIVITY;
+    const int32_t waves = 4 * (plain ? 4 : 3) * 64 / lc.threads;
+    return std::max(1, std::min(waves, (int32_t)(kLdsPerCu / (lc.lds + kLdsStatic))));
+}
+
+// The LDS records and winner table of each class.  What they cost is
+// residency: a batch of few searches takes as long as its longest and wants
+// every record that a round can use; a batch of many takes its searches'
+// total time over those that run at once.  Three sizes, the same for all
+// classes: all records and twice as many table entries; half of both; one
+// record per thread (128 at least) and 256 entries.  The largest is taken at
+// which either the GPU holds every search at once, or the searches, each
+// weighted by its variables over those of the largest (the mean of the largest
+// sixteenth: about how its time compares with the longest), need at most 0.7 of
+// the CUs: then the others are done while the longest run.  (Searches of one
+// length in two turns need more than 1 on this scale; the rest is for their
+// spread.)  Where not even the least does, each class takes the most that
+// leaves a CU as many of its searches.
+// Measured, the three sizes in turn (weighted need): uneven random programs
+// of 100..5000 atoms, 128 threads, 512 of them 407, 404 and 442 ms (0.34, 0.17,
+// 0.09); 1024, 428, 445 and 490 (0.68, 0.35, 0.17); 1536, 542, 545 and 614 (1.0,
+// 0.52, 0.26); 2048, 653, 561 and 632 (1.3, 0.69, 0.34); 3072, 922, 613 and 671
+// (2.0, 1.05, 0.52); 4096 with 256 threads for the largest, 4191, 2555 and 1960
+// (2.7, 1.4, 0.77).  300 programs of 45 to 64 thousand variables: 495, 352, 403.
+void size_tables(Plan& P) {
+    struct Most {
+        int32_t fc, wbits;
+    };
+    std::vector<LaunchClass>& C = P.classes;
+    std::vector<Most> most;
+    auto fit = [&](LaunchClass& lc, int32_t fc, int32_t wbits) {
+        lc.fc = fc;
+        lc.wbits = wbits;
+        lc.lds = lds_bytes(lc.threads, fc, wbits, lc.words, lc.awords, lc.owords, P.learning);
+    };
+    auto twice = [](int32_t fc) { return fc <= 128 ? 8 : fc <= 256 ? 9 : fc <= 512 ? 10 : 11; };
+    auto least = [](const LaunchClass& lc) { return std::max(lc.threads, 128); };
+    for (LaunchClass& lc : C) {
+        // no more than one workgroup can hold: what needs all the LDS gets one
+        // record per thread and 256 entries, and the learned-occurrence bits
+        // only where they fit, so that no program is refused for them
+        for (fit(lc, lc.fc, twice(lc.fc)); lc.lds > kLdsPerGroup && lc.fc > least(lc);)
+            fit(lc, lc.fc / 2, lc.wbits - 1);
+        if (lc.lds > kLdsPerGroup) fit(lc, lc.fc, 8);
+        if (lc.lds > kLdsPerGroup) {
+            lc.owords = 0;
+            fit(lc, lc.fc, 8);
+        }
+        most.push_back({lc.fc, lc.wbits});
+    }
+    const double largest = std::max(1.0, P.Vtop);
+    for (int level = 0; level < 3; ++level) {
+        double need = 0, weighted = 0;
+        for (size_t i = 0; i < C.size(); ++i) {
+            LaunchClass& lc = C[i];
+            if (level == 1) fit(lc, std::max(least(lc), most[i].fc / 2), std::max(8, most[i].wbits - 1));
+            if (level == 2) fit(lc, least(lc), 8);
+            need += (double)lc.count / per_cu(P, lc);
+            weighted += (double)lc.vsum / largest / per_cu(P, lc);
+        }
+        if (need <= kCUs || weighted <= 0.7 * kCUs) return;
+    }
+    for (size_t i = 0; i < C.size(); ++i) {
+        LaunchClass& lc = C[i];
+        const int32_t held = per_cu(P, lc);
+        bool found = false;
+        for (int32_t fc = most[i].fc; fc >= least(lc) && !found; fc /= 2)
+            for (int32_t w = std::min(twice(fc), most[i].wbits); w >= std::max(8, twice(fc) - 1) && !found; --w) {
+                fit(lc, fc, w);
+                found = per_cu(P, lc) >= held;
+            }
+        if (!found) fit(lc, least(lc), 8);
     }
 }
 
@@ -279,9 +361,10 @@ int32_t make_plan(const std::vector<const HostProgram*>& progs, const asp_option
         LaunchClass lc;
         lc.first = k;
         const int c = cls(P.order[k]);
-        int64_t vmax = 0, amax = 0, omax = 0;
+        int64_t vmax = 0, amax = 0, omax = 0, vsum = 0;
         while (k < P.n && cls(P.order[k]) == c) {
             vmax = std::max<int64_t>(vmax, progs[P.order[k]]->V);
+            vsum += progs[P.order[k]]->V;
             amax = std::max<int64_t>(amax, progs[P.order[k]]->A);
             omax = std::max<int64_t>(omax, (int64_t)progs[P.order[k]]->A + progs[P.order[k]]->Rh);
             ++k;
@@ -291,29 +374,17 @@ int32_t make_plan(const std::vector<const HostProgram*>& progs, const asp_option
         lc.awords = (int32_t)((amax + 1 + 31) / 32);
         const int ci = (int)P.classes.size();
         lc.threads = (class_threads && ci < 4 && class_threads[ci] > 0) ? class_threads[ci] : threads;
-        // the learned-occurrence bits (Fwd-learning) only where they fit: a
-        // program that fits the LDS without them is not refused for them
         lc.owords = P.learning == ASP_LEARN_FWD ? (int32_t)((omax + 1 + 31) / 32) : 0;
-        const int32_t least = std::max(lc.threads, 128);
-        lc.fc = std::max(least, front_records(vmax));
-        // (twice as many winner-table entries as records, 256 at least; what
-        // needs all the LDS gets one record per thread and 256 entries)
-        lc.wbits = lc.fc <= 128 ? 8 : lc.fc <= 256 ? 9 : lc.fc <= 512 ? 10 : 11;
-        auto fit = [&] { lc.lds = lds_bytes(lc.threads, lc.fc, lc.wbits, lc.words, lc.awords, lc.owords, P.learning); };
-        for (fit(); lc.lds > kLdsPerGroup && lc.fc > least; fit()) {
-            lc.fc /= 2;
-            lc.wbits -= 1;
-        }
-        if (lc.lds > kLdsPerGroup) {
-            lc.wbits = 8;
-            fit();
-        }
-        if (lc.lds > kLdsPerGroup) {
-            lc.owords = 0;
-            fit();
-        }
+        lc.fc = std::max(std::max(lc.threads, 128), front_records(vmax));
+        lc.vsum = vsum;
         P.classes.push_back(lc);
     }
+    std::vector<int64_t> vs;
+    for (auto* h : progs) vs.push_back(h->V);
+    const size_t top = (vs.size() + 15) / 16;
+    std::partial_sort(vs.begin(), vs.begin() + top, vs.end(), std::greater<int64_t>());
+    P.Vtop = (double)std::accumulate(vs.begin(), vs.begin() + top, (int64_t)0) / (double)top;
+    size_tables(P);
     uint64_t o = 0;
     auto take = [&](uint64_t bytes) {
         uint64_t at = o;
@@ -1682,6 +1753,19 @@ int32_t asp_batch_launch_info(asp_batch* b, int32_t* n_classes, int32_t* first, 
         }
     }
     if (order) memcpy(order, P.order.data(), 4 * P.order.size());
+    return ASP_OK;
+}
+
+int32_t asp_batch_launch_lds(const asp_batch* b, int32_t* per_cu_out, int64_t* lds, int32_t* records,
+                             int32_t* table) {
+    if (!b) return fail(ASP_E_INVALID, "null batch");
+    for (size_t c = 0; c < b->plan.classes.size(); ++c) {
+        const LaunchClass& lc = b->plan.classes[c];
+        if (per_cu_out) per_cu_out[c] = per_cu(b->plan, lc);
+        if (lds) lds[c] = (int64_t)lc.lds;
+        if (records) records[c] = lc.fc;
+        if (table) table[c] = 1 << lc.wbits;
+    }
     return ASP_OK;
 }
 
