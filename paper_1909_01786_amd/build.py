@@ -1,8 +1,8 @@
 """Build libasp.so (HIP for gfx950) in-tree with hipcc.
 
 The library is the product path: ``csrc/encode.cpp`` (host encoding),
-``csrc/solver.hip`` (device search), ``csrc/scorer.hip`` (learned Decision
-scorer), ``csrc/trainer.hip`` and ``csrc/train.cpp`` (its training) and
+``csrc/solver.hip`` and ``csrc/solver_wide.hip`` (device search, with Deps of
+one word and of several), ``csrc/scorer.hip`` (learned Decision scorer), ``csrc/trainer.hip`` and ``csrc/train.cpp`` (its training) and
 ``csrc/api.cpp`` (C ABI of ``include/asp.h``).  Packed FP32 instructions are disabled for every HIP
 translation unit.
 """
@@ -17,7 +17,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libasp.so")
-SOURCES = ["encode.cpp", "api.cpp", "train.cpp", "solver.hip", "scorer.hip", "trainer.hip"]
+SOURCES = ["encode.cpp", "api.cpp", "train.cpp", "solver.hip", "solver_wide.hip", "scorer.hip", "trainer.hip"]
 HEADERS = ["encode.h", "layout.h", "scorer.h", "train.h", "trainer.h"]
 ARCH = os.environ.get("ASP_OFFLOAD_ARCH", "gfx950")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -26,7 +26,7 @@
 namespace asp {
 size_t lds_bytes(int threads, int fc, int wbits, int words, int awords, int owords, int learning);
 hipError_t launch_search(const KArgs& a, int threads, int grid, size_t lds, hipStream_t s);
-hipError_t set_max_lds(int threads, size_t lds);
+hipError_t set_max_lds(const KArgs& a, int threads, size_t lds);
 }  // namespace asp
 
 using namespace asp;
@@ -249,6 +249,11 @@ void size_tables(Plan& P) {
     auto twice = [](int32_t fc) { return fc <= 128 ? 8 : fc <= 256 ? 9 : fc <= 512 ? 10 : 11; };
     auto least = [](const LaunchClass& lc) { return std::max(lc.threads, 128); };
     for (LaunchClass& lc : C) {
+        if (P.W > 1) {                      // the kernel's fixed layout
+            lc.owords = 0;
+            fit(lc, wide_records(lc.threads), kWideBits);
+            continue;
+        }
         // no more than one workgroup can hold: what needs all the LDS gets one
         // record per thread and 256 entries, and the learned-occurrence bits
         // only where they fit, so that no program is refused for them
@@ -261,6 +266,7 @@ void size_tables(Plan& P) {
         }
         most.push_back({lc.fc, lc.wbits});
     }
+    if (P.W > 1) return;
     const double largest = std::max(1.0, P.Vtop);
     for (int level = 0; level < 3; ++level) {
         double need = 0, weighted = 0;
@@ -462,6 +468,20 @@ int32_t upload_static(const std::vector<const HostProgram*>& progs, const Plan& 
     return ASP_OK;
 }
 
+// The options of a plan's searches, which select the kernel.
+void set_mode(KArgs& a, const Plan& P) {
+    a.W = P.W;
+    a.gate_mode = P.gate;
+    a.decision = P.decision;
+    a.fallback_after = P.fallback_after;
+    a.learning = P.learning;
+    a.max_models = P.max_models;
+    a.learn_k = P.learn_k;
+    a.restart_every = P.restart_every;
+    a.model_store = P.model_store;
+    a.lookahead = P.lookahead;
+}
+
 KArgs make_args(const Plan& P, uint8_t* arena, int32_t mode, const LaunchClass& lc) {
     KArgs a{};
     a.inst = (const InstDesc*)(arena + P.off_desc);
@@ -484,16 +504,7 @@ KArgs make_args(const Plan& P, uint8_t* arena, int32_t mode, const LaunchClass& 
     a.verdicts = (int32_t*)(arena + P.off_verd);
     a.stats = (DevStats*)(arena + P.off_stats);
     a.models = arena + P.off_models;
-    a.W = P.W;
-    a.gate_mode = P.gate;
-    a.decision = P.decision;
-    a.fallback_after = P.fallback_after;
-    a.learning = P.learning;
-    a.max_models = P.max_models;
-    a.learn_k = P.learn_k;
-    a.restart_every = P.restart_every;
-    a.model_store = P.model_store;
-    a.lookahead = P.lookahead;
+    set_mode(a, P);
     a.words = lc.words;
     a.awords = lc.awords;
     a.owords = lc.owords;
@@ -577,8 +588,10 @@ int32_t check_launch(const Plan& P, const DeviceInfo& di) {
         return fail(ASP_E_CAPACITY, "largest instance needs " + std::to_string(P.max_lds()) +
                                         " bytes of LDS, device allows " +
                                         std::to_string(di.max_lds));
+    KArgs a{};
+    set_mode(a, P);
     for (const LaunchClass& c : P.classes)
-        (void)set_max_lds(c.threads, c.lds);  // best effort: older runtimes ignore it
+        (void)set_max_lds(a, c.threads, c.lds);  // best effort: older runtimes ignore it
     return ASP_OK;
 }
 

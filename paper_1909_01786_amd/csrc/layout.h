@@ -208,4 +208,9 @@ struct KArgs {
     int32_t wbits, pad2;         // log2 of the LDS winner table's entries
 };
 
+// With Deps of several words, a search's frontier records and the log2 of its
+// winner table's entries: fixed, so that the kernel's LDS offsets are constants.
+constexpr int32_t kWideBits = 8;
+constexpr int32_t wide_records(int32_t threads) { return threads > 128 ? threads : 128; }
+
 }  // namespace asp

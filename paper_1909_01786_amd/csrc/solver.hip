@@ -159,6 +159,7 @@ struct Ctx {
     int32_t ext;            // extended search: several answer sets, restarts, activity,
                             // several conflicts learned per step (compile-time in k_search)
     int32_t multi;          // several conflicts learned per step (compile-time in k_search)
+    int32_t one;            // W = 1 (compile-time in k_search)
     int32_t learn_k;        // round conflicts learned per step
     int32_t lookahead;      // Decision candidates tried by propagation (extended search)
     unsigned long long my_visits, my_checks;
@@ -982,33 +983,25 @@ DEV void step_round(Ctx& c, Ctl& k) {
     c.scr->tail = qt;
     c.scr->nimpl = 0;
     bar();
-    // pass 0 classifies, pass 1 (after a clash) finds the impliers that lost,
-    // pass 2 selects the next conflict, when several are learned per step:
-    // the next smallest keys, one pass each, on the same snapshot and winners
+    // each pass ends with a barrier
+    visit_pass(c, k, qh, qt, 0);
+    if (uni(c.scr->clash)) visit_pass(c, k, qh, qt, 1);
+    // several conflicts learned per step: the next smallest keys, one
+    // selection pass each, on the same snapshot and winners
     int nsel = 1;
-    unsigned long long thr = ~0ull;
-#pragma unroll 1
-    for (int pass = 0;;) {
-        visit_pass(c, k, qh, qt, pass);    // ends with a barrier
-        if (pass == 0 && uni(c.scr->clash)) {
-            pass = 1;
-            continue;
-        }
-        if (!c.multi || c.learn_k <= 1) break;
-        if (pass < 2) {
-            thr = (unsigned long long)uni64((int64_t)c.scr->conf_key);
-            pass = 2;
-        } else {
+    if (c.multi && c.learn_k > 1) {
+        unsigned long long thr = (unsigned long long)uni64((int64_t)c.scr->conf_key);
+        while (nsel < c.learn_k && thr != ~0ull) {
+            c.scr->conf_key2 = ~0ull;      // identical from every lane
+            c.scr->conf_thr = thr;
+            bar();
+            visit_pass(c, k, qh, qt, 2);
             thr = (unsigned long long)uni64((int64_t)c.scr->conf_key2);
             bar();                         // every lane has read it
             if (thr == ~0ull) break;
             k.pend_more[nsel - 1] = (int32_t)(uint32_t)(thr & 0xffffffffull);
             nsel += 1;
         }
-        if (nsel >= c.learn_k || thr == ~0ull) break;
-        c.scr->conf_key2 = ~0ull;          // identical from every lane
-        c.scr->conf_thr = thr;
-        bar();
     }
     const int nt = uni(c.scr->tail);
     // apply every implication, its Deps being the OR of the Deps of the
@@ -1565,7 +1558,7 @@ DEV int wave_rounds(Ctx& c, Ctl& k, int max_rounds) {
 
 // Up to max_rounds rounds from the current frontier; returns how many.
 DEV int step_rounds(Ctx& c, Ctl& k, int max_rounds) {
-    if (c.W == 1 && k.fr_ok && !k.fr_big && k.qt - k.qh <= kWaveVisits) {
+    if (c.one && k.fr_ok && !k.fr_big && k.qt - k.qh <= kWaveVisits) {
         int n;
         switch (c.FC) {
         case 128: n = wave_rounds<128>(c, k, max_rounds); break;
@@ -2488,7 +2481,7 @@ DEV void run_search(Ctx& c, Ctl& k, const KArgs& a, uint8_t* model, uint64_t t0)
             }
             // the clock is read per wave, every 64 steps (or run of rounds);
             // the workgroup acts on the OR
-            if (k.steps >= next_clock) {
+            if (c.one ? k.steps >= next_clock : (k.steps & 63) == 0) {
                 next_clock = k.steps + 64;
                 int late = (a.max_ticks && (uint64_t)(wall_clock64() - t0) > a.max_ticks) ? 1 : 0;
                 if (block_any(c, late)) k.status = ST_E_TIMEOUT;
@@ -2574,18 +2567,25 @@ DEV void write_result(Ctx& c, const Ctl& k, const KArgs& a, uint64_t t0) {
 // Four waves per SIMD for the plain search with Fwd-learning: the register
 // budget (128 VGPRs) at which it keeps eight 128-thread workgroups resident
 // per CU (LDS allowing); Res-learning and the extended search, with more
-// live state, keep three (168 VGPRs) rather than spill.  The Learning
+// live state, keep three (168 VGPRs).  The Learning
 // step and the search mode are compile-time parameters -- EN 0 plain, 1
 // extended (several answer sets, restarts, the activity Decision), 2 the
-// extended search learning several conflicts per step -- so each search
-// carries only its own code and registers.
-template <int MAXT, int LR, int EN>
+// extended search learning several conflicts per step -- and so is W = 1
+// (ONE), so each search carries only its own code and registers.  At W = 1 the
+// call of the one-wave rounds has the search's state live across it: 62 VGPRs
+// spill in the plain search, 4 under Res-learning, 18 to 50 in the extended
+// ones (at 128 threads).  Wider Deps never take that path.  Compiled with it
+// they spilled 124 and 16, and a 2000-vertex colouring took 97.7 ms at W = 2, 128
+// Hamiltonian-cycle programs 61.5; without it, and with an LDS layout fixed at
+// compile time, nothing spills below 1024 threads: 89.8 and 54.9 ms.
+template <int MAXT, int LR, int EN, bool ONE>
 __global__ __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu((EN == 0 && LR == 0) ? 4 : 3))) void k_search(KArgs a) {
     HIP_DYNAMIC_SHARED(uint4, smem16);     // 16-byte aligned base
     __shared__ Scr scr;
     Ctx c;
     Ctl k;
-    c.W = a.W;
+    c.W = ONE ? 1 : a.W;
+    c.one = ONE;
     c.decision = a.decision;
     c.fallback_after = a.fallback_after;
     c.learning = LR;
@@ -2598,14 +2598,14 @@ __global__ __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu((EN == 0 &
     c.lane = threadIdx.x & 63;
     c.wid = threadIdx.x >> 6;
     c.nw = MAXT / 64;
-    c.FC = a.fc;
-    c.wbits = a.wbits;
+    c.FC = ONE ? a.fc : wide_records(MAXT);
+    c.wbits = ONE ? a.wbits : kWideBits;
     c.scr = &scr;
     c.my_visits = c.my_checks = 0ull;
     {
         // the arrays of LdsMap<FC>
         unsigned char* p = (unsigned char*)smem16;
-        const size_t fc = (size_t)a.fc, wc = (size_t)1 << a.wbits;
+        const size_t fc = (size_t)c.FC, wc = (size_t)1 << c.wbits;
         c.base = p;
         c.sB = (unsigned long long*)p; p += 8 * kMaxW;
         c.iDeps = (unsigned long long*)p; p += 8 * fc;
@@ -2631,8 +2631,9 @@ __global__ __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu((EN == 0 &
         c.sOff = (int32_t*)p; p += sizeof(int32_t) * MAXT;
         c.valb = (uint32_t*)p; p += sizeof(uint32_t) * a.words;
         c.lm = (uint32_t*)p; p += sizeof(uint32_t) * a.awords;
-        // Fwd-learning, where LDS has room for it
-        c.occb = LR != LEARN_RES && a.owords > 0 ? (uint32_t*)p : nullptr;
+        // Fwd-learning at W = 1 (one-wave rounds alone read it), where LDS has
+        // room for it
+        c.occb = ONE && LR != LEARN_RES && a.owords > 0 ? (uint32_t*)p : nullptr;
     }
     const uint64_t t0 = wall_clock64();
     int inst = 0;
@@ -2652,6 +2653,45 @@ __global__ __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu((EN == 0 &
 }
 
 // ------------------------------------------------------------ launchers
+typedef void (*SearchFn)(KArgs);
+
+template <int LR, int EN, bool ONE>
+static SearchFn search_fn_v(int threads) {
+    switch (threads) {
+    case 64: return k_search<64, LR, EN, ONE>;
+    case 128: return k_search<128, LR, EN, ONE>;
+    case 256: return k_search<256, LR, EN, ONE>;
+    case 512: return k_search<512, LR, EN, ONE>;
+    case 1024: return k_search<1024, LR, EN, ONE>;
+    default: return nullptr;
+    }
+}
+
+template <int LR, bool ONE>
+static SearchFn search_fn_lr(const KArgs& a, int threads) {
+    if (a.learn_k > 1) return search_fn_v<LR, 2, ONE>(threads);
+    if (a.max_models != 1 || a.restart_every != 0 || a.decision == DECISION_ACTIVITY || a.lookahead > 1)
+        return search_fn_v<LR, 1, ONE>(threads);
+    return search_fn_v<LR, 0, ONE>(threads);
+}
+
+template <bool ONE>
+static SearchFn search_fn(const KArgs& a, int threads) {
+    if (a.learning == LEARN_FWD) return search_fn_lr<LEARN_FWD, ONE>(a, threads);
+    if (a.learning == LEARN_RES) return search_fn_lr<LEARN_RES, ONE>(a, threads);
+    return nullptr;
+}
+
+// The kernel of a launch, or null.  Those for W = 1 and for wider Deps are
+// compiled apart (solver_wide.hip), side by side.
+SearchFn search_fn_wide(const KArgs& a, int threads);
+#ifdef ASP_WIDE
+SearchFn search_fn_wide(const KArgs& a, int threads) { return search_fn<false>(a, threads); }
+#else
+static SearchFn search_kernel(const KArgs& a, int threads) {
+    return a.W == 1 ? search_fn<true>(a, threads) : search_fn_wide(a, threads);
+}
+
 size_t lds_bytes(int threads, int fc, int wbits, int words, int awords, int owords, int learning) {
     const size_t f = (size_t)fc, wc = (size_t)1 << wbits;
     return sizeof(uint32_t) * ((size_t)words + (size_t)awords + (size_t)owords) +
@@ -2661,77 +2701,18 @@ size_t lds_bytes(int threads, int fc, int wbits, int words, int awords, int owor
            sizeof(unsigned long long) * (learning == LEARN_RES ? (size_t)threads : 0);
 }
 
-template <int LR, int EN>
-static hipError_t launch_v(const KArgs& a, int threads, int grid, size_t lds, hipStream_t s) {
-    switch (threads) {
-    case 64: hipLaunchKernelGGL((k_search<64, LR, EN>), dim3(grid), dim3(64), lds, s, a); break;
-    case 128: hipLaunchKernelGGL((k_search<128, LR, EN>), dim3(grid), dim3(128), lds, s, a); break;
-    case 256: hipLaunchKernelGGL((k_search<256, LR, EN>), dim3(grid), dim3(256), lds, s, a); break;
-    case 512: hipLaunchKernelGGL((k_search<512, LR, EN>), dim3(grid), dim3(512), lds, s, a); break;
-    case 1024: hipLaunchKernelGGL((k_search<1024, LR, EN>), dim3(grid), dim3(1024), lds, s, a); break;
-    default: return hipErrorInvalidValue;
-    }
+hipError_t launch_search(const KArgs& a, int threads, int grid, size_t lds, hipStream_t s) {
+    const SearchFn f = search_kernel(a, threads);
+    if (!f) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(f, dim3(grid), dim3(threads), lds, s, a);
     return hipGetLastError();
 }
 
-static int search_mode(const KArgs& a) {
-    if (a.learn_k > 1) return 2;
-    return (a.max_models != 1 || a.restart_every != 0 || a.decision == DECISION_ACTIVITY ||
-            a.lookahead > 1) ? 1 : 0;
+hipError_t set_max_lds(const KArgs& a, int threads, size_t lds) {
+    const SearchFn f = search_kernel(a, threads);
+    if (!f) return hipErrorInvalidValue;
+    return hipFuncSetAttribute((const void*)f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
 }
-
-template <int LR>
-static hipError_t launch_lr(const KArgs& a, int threads, int grid, size_t lds, hipStream_t s) {
-    switch (search_mode(a)) {
-    case 0: return launch_v<LR, 0>(a, threads, grid, lds, s);
-    case 1: return launch_v<LR, 1>(a, threads, grid, lds, s);
-    default: return launch_v<LR, 2>(a, threads, grid, lds, s);
-    }
-}
-
-hipError_t launch_search(const KArgs& a, int threads, int grid, size_t lds, hipStream_t s) {
-    if (a.learning == LEARN_FWD) return launch_lr<LEARN_FWD>(a, threads, grid, lds, s);
-    if (a.learning == LEARN_RES) return launch_lr<LEARN_RES>(a, threads, grid, lds, s);
-    return hipErrorInvalidValue;
-}
-
-template <int LR, int EN>
-static const void* search_fn_v(int threads) {
-    switch (threads) {
-    case 64: return (const void*)k_search<64, LR, EN>;
-    case 128: return (const void*)k_search<128, LR, EN>;
-    case 256: return (const void*)k_search<256, LR, EN>;
-    case 512: return (const void*)k_search<512, LR, EN>;
-    case 1024: return (const void*)k_search<1024, LR, EN>;
-    default: return nullptr;
-    }
-}
-
-template <int LR>
-static const void* search_fn_lr(int threads, int en) {
-    switch (en) {
-    case 0: return search_fn_v<LR, 0>(threads);
-    case 1: return search_fn_v<LR, 1>(threads);
-    default: return search_fn_v<LR, 2>(threads);
-    }
-}
-
-static const void* search_fn(int threads, int learning, int en) {
-    if (learning == LEARN_FWD) return search_fn_lr<LEARN_FWD>(threads, en);
-    if (learning == LEARN_RES) return search_fn_lr<LEARN_RES>(threads, en);
-    return nullptr;
-}
-
-hipError_t set_max_lds(int threads, size_t lds) {
-    for (int lr : {(int)LEARN_FWD, (int)LEARN_RES})
-        for (int en = 0; en < 3; ++en) {
-            const void* f = search_fn(threads, lr, en);
-            if (!f) return hipErrorInvalidValue;
-            const hipError_t e =
-                hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            if (e != hipSuccess) return e;
-        }
-    return hipSuccess;
-}
+#endif
 
 }  // namespace asp

@@ -90,3 +90,12 @@ def test_residency_rule(P, seed):
         classes = int(rng.integers(1, 5))
         b = P.Batch(progs, threads=cth[-1], classes=classes, class_threads=cth)
         _check(b, [g.n_vars for g in progs], 12 if mode else 16)
+
+
+@pytest.mark.parametrize("threads", [64, 128, 256, 1024])
+@pytest.mark.parametrize("n", [1, 3000])
+def test_wide_deps_take_the_least(P, n, threads):
+    """Searches with Deps of several words have one layout."""
+    g = P.Program(_facts(44000), W=2)
+    (held, lds, rec, tab), = _check(P.Batch([g] * n, threads=threads), [g.n_vars] * n, 16)
+    assert (rec, tab) == (max(threads, 128), 256)
