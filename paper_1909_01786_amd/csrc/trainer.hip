@@ -514,12 +514,15 @@ __global__ __launch_bounds__(NT) void k_readout(const float* A, const float* y, 
 }
 
 // The readout's sums: each column one float32 running sum over the waves'
-// partials, in their order.  What a long running sum rounds away, all the same
-// way, is up to 3e-5 of the loss and of the last bias's gradient at 0.8M rows:
-// a sum over a tree leaves it out and moves both by that much, so the order is
-// part of the result.  One workgroup: a thread per column adds a chunk in LDS
-// while all threads load the next.  The chain of additions bounds it (48
-// thousand partials on 64 programs; their loads alone would take 5 us).
+// partials, in their order, so that two runs give the same bits.  A running
+// sum this long rounds: at 0.8M rows the loss and the last bias's gradient are
+// 1e-5 to 4e-5 from a sum over a tree, which is nearer to the exact value and
+// has no serial chain.  It is kept because these sums were running ones before
+// (atomics, in the order of arrival): losses and Adam steps stay within
+// rounding of those of earlier training runs, and a tree moved them by more.
+// One workgroup: a thread per column adds a chunk in LDS while all threads
+// load the next.  The chain of additions bounds it (48 thousand partials on
+// 64 programs; their loads alone would take 5 us).
 constexpr int kRunRows = 128, kRunT = 1024;
 __global__ __launch_bounds__(kRunT) void k_running_sums(const float* part, int64_t n, TrSegs sg) {
     __shared__ __attribute__((aligned(16))) float buf[2][kRunRows * kReadout];
