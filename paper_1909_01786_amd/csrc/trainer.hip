@@ -31,7 +31,7 @@
 // is, to float32 rounding.
 // Measured on 64 programs (0.77M variable rows, 2.0M nogood rows, 4.6M edges):
 // 63 ms a step with a kernel per product, edge sum and activation (75 of
-// them, the column sums by atomics on 64 addresses), 10.2 ms so.
+// them, the column sums by atomics on 64 addresses), 10.6 ms so.
 //
 // Row arrays are [rows][64] float32, row-major.  Matrices are [in][out].
 #include <hip/hip_runtime.h>
